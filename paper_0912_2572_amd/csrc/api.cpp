@@ -740,9 +740,8 @@ int fork_join_for_current_device(ForkJoin **out) {
 
 // The fork/join schedule of tsqr_factor_solve for a single-panel FP64
 // factor (caller holds g_fork_mu).  main: leaf, tree, signs, thin Q.  aux:
-// after the leaf, the chunks' T factors and the solve's copy and leaf pass
-// of Q^T B; after the tree, its tree pass and the triangular solve.  main
-// finally waits for aux.
+// after the leaf, the solve's copy and leaf pass of Q^T B; after the tree,
+// its tree pass and the triangular solve.  main finally waits for aux.
 int factor_solve_forked(tsqr_factors_s *f, const double *A, int64_t lda, int64_t k, const double *B,
                         int64_t ldb, double *X, int64_t ldx, double *resid, int32_t *dinfo, double *Q,
                         int64_t ldq, hipStream_t st, const ForkJoin &fj) {
@@ -758,13 +757,9 @@ int factor_solve_forked(tsqr_factors_s *f, const double *A, int64_t lda, int64_t
     if (!p.wchunk0.empty())
         TRY(hipMemcpyAsync(f->ws + p.off_wtab, p.wchunk0.data(), sizeof(int64_t) * p.wchunk0.size(),
                            hipMemcpyHostToDevice, st));
-    TRY(tsqr::launch_leaf(A, lda, W, P.m, Tc, Rdom, pa, 2, st));
+    TRY(tsqr::launch_leaf(A, lda, W, P.m, Tc, Rdom, pa, 1, st));
     TRY(hipEventRecord(fj.leaf, st));
     TRY(hipStreamWaitEvent(fj.aux, fj.leaf, 0));
-    // the chunks' T factors (the leaf stored their Gram entries), beside the
-    // tree: the tree does not read them; the solve's leaf pass and the thin
-    // Q's leaf kernel (after fj.done) do
-    TRY(tsqr::launch_chunk_t(Tc, pa, p.total_chunks, fj.aux));
     TRY(tsqr::launch_copy(B, ldb, C, P.m, P.m, k, fj.aux));
     TRY(leaf_apply(f, p, C, P.m, C, P.m, k, 1, fj.aux));
     for (const auto &L : levels) {
