@@ -171,7 +171,7 @@ int enqueue(tsqr_batch_s *B, hipStream_t st, int *launches) {
             TRYB(tsqr::launch_tree_b(D, L(g), g.cnt, g.up[lv], g.ns, lv, st));
             ++nl;
         }
-        TRYB(tsqr::launch_tree_t_b(D, L(g), g.cnt, g.maxP, st));
+        TRYB(tsqr::launch_tree_t_b(D, L(g), g.cnt, g.maxP, g.ns, st));
         ++nl;
     }
     const Group &A = B->all;

@@ -284,9 +284,9 @@ __device__ __forceinline__ void leaf_domain(LeafSmem<NS> &sm, const double *__re
         auto none = [](auto) {};
         if constexpr (KIND != kFull) {
             if constexpr (FIRST) issue_pairs<NT, VEC, 0, PAIRS>(nx, column_or_zeros<NT>(pA + ROWS, lda, n, 0, more, la));
-            panel_qr<kLeafWaves, NS, NT, FIRST, false, false>(c, n, sm, want_t, none, none, done, t_block);
+            panel_qr<kLeafWaves, NS, NT, FIRST, false>(c, n, sm, want_t, none, none, done, t_block);
         } else {
-            panel_qr<kLeafWaves, NS, NT, false, false, true>(c, n, sm, want_t, load, store, done, t_block);
+            panel_qr<kLeafWaves, NS, NT, false, true>(c, n, sm, want_t, load, store, done, t_block);
         }
         pA += ROWS;
         pV += ROWS;

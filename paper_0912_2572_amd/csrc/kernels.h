@@ -91,8 +91,6 @@ struct TreePath {
     int64_t span[kMaxTreeLevels];
 };
 
-size_t factor_smem_bytes();
-
 // ---------------------------------------------------------------------------
 // Batched path: one descriptor per matrix (single panel, n <= 64, one
 // right-hand side), resident in device memory.  Batched kernels take a list
@@ -137,9 +135,10 @@ hipError_t launch_leaf(const double *A, int64_t lda, double *V, int64_t ldv, dou
                        const PanelArgs &pa, int keep_q, hipStream_t st);
 hipError_t launch_tree_level(double *Rdom, double *Tnode, const PanelArgs &pa, const TreeArgs &ta,
                              int keep_q, hipStream_t st);
-// T of every tree node (nodes 1 .. P - 1) from the Gram entries and tau the
-// levels stored; launched once after the last level when Q is kept.
-hipError_t launch_tree_t(double *Tnode, const PanelArgs &pa, hipStream_t st);
+// T of every tree node (nodes 1 .. P - 1) from its reflector block and the
+// panels' T the levels stored; launched once after the last level when Q is
+// kept.
+hipError_t launch_tree_t(const double *Rdom, double *Tnode, const PanelArgs &pa, hipStream_t st);
 // The same leaf with the reflectors stored in FP32 (mixed precision).
 hipError_t launch_leaf32(const double *A, int64_t lda, float *V, int64_t ldv, double *Tc, double *Rdom,
                          const PanelArgs &pa, int keep_q, hipStream_t st);
@@ -254,7 +253,7 @@ hipError_t launch_mixed_final(const double *R, int n, int k, const double *Xw, d
 hipError_t launch_leaf_b(const BMat *mats, const int *list, int cnt, int64_t gx, int ns, hipStream_t st);
 hipError_t launch_tree_b(const BMat *mats, const int *list, int cnt, int64_t gx, int ns, int level,
                          hipStream_t st);
-hipError_t launch_tree_t_b(const BMat *mats, const int *list, int cnt, int64_t maxP, hipStream_t st);
+hipError_t launch_tree_t_b(const BMat *mats, const int *list, int cnt, int64_t maxP, int ns, hipStream_t st);
 hipError_t launch_sign_b(const BMat *mats, const int *list, int cnt, hipStream_t st);
 // Q^T (trans = 1) or Q (trans = 0) on F, leaves, in three chunk-parallel
 // passes (grid.x: max_chunks for passes 1 and 3, max_p for pass 2); sweep > 0

@@ -60,13 +60,12 @@ struct PanelSmem {
     static constexpr int kLd = 16 * NS + 1;        // row stride of R and T (odd)
     static constexpr int kVtLd = 16 * NT + 4;      // column stride of the row operands
     alignas(32) double R[16 * NS * kLd];           // running triangle, row-major
-    double T[W > 1 ? 16 * NS * kLd : 16 * 17];     // W > 1: T of the block, Gram blocks below its
-                                                   // diagonal blocks; W = 1: the panel's T
+    double T[16 * NS * kLd];                       // the block's T
     alignas(32) double red[2][16 * W];             // per-wave dots of the panel's columns
     double redq[2][16];                            // pivot-row values (first block)
     alignas(32) double vt[NS > 1 ? W * 16 * kVtLd : 1];   // V of the panel by columns, a region per wave
     alignas(32) double part[(NS > 1 && W > 1) ? (NS - 1) * W * 256 : 1];   // per-wave V^T C
-    double P[NS > 1 && W > 1 ? 16 * NS * 16 : 1];  // scratch of the block's T
+    double P[NS > 1 ? 16 * NS * 16 : 1];           // scratch of the block's T
 };
 
 // The step's dots over four tiles, s_r += x c with x = the register of lane Q
@@ -100,6 +99,26 @@ __device__ __forceinline__ void tile_axpy(d4 &c, d4 &d, double f) {
 #undef TSQR_AXPY
     c = d4{c0, c1, c2, c3};
     d = d4{d0, d1, d2, d3};
+}
+
+// The same for one tile.
+template <int Q>
+__device__ __forceinline__ void tile_dots(double (&s)[4], const d4 &c) {
+#define TSQR_DOT(acc, x) "v_fmac_f64_dpp %" #acc ", %" #x ", %" #x " row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+    asm("s_nop 1\n\t" TSQR_DOT(0, 4) TSQR_DOT(1, 5) TSQR_DOT(2, 6) TSQR_DOT(3, 7)
+        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3])
+        : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]), "n"(Q));
+#undef TSQR_DOT
+}
+template <int Q>
+__device__ __forceinline__ void tile_axpy(d4 &c, double f) {
+#define TSQR_AXPY(x) "v_fmac_f64_dpp %" #x ", %" #x ", %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+    double c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3];
+    asm("s_nop 1\n\t" TSQR_AXPY(0) TSQR_AXPY(1) TSQR_AXPY(2) TSQR_AXPY(3)
+        : "+v"(c0), "+v"(c1), "+v"(c2), "+v"(c3)
+        : "v"(f), "n"(Q));
+#undef TSQR_AXPY
+    c = d4{c0, c1, c2, c3};
 }
 
 // Sum over the four lane rows (lanes cg, cg + 16, cg + 32, cg + 48), the
@@ -157,6 +176,16 @@ struct PanelRegs {
     double gq, tau;    // last step's Gram entry of this lane's column, and its tau
 };
 
+__device__ __forceinline__ void panel_begin(PanelRegs &pr) {
+    pr.scale = 1.0;
+    pr.gq = 0.0;
+    pr.tau = 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) pr.trow[q] = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) pr.rrow[u] = 0.0;
+}
+
 // Column J of the panel's T (rows on lanes) from the Gram entries of step J:
 // T[0:J, J] = -tau_J T[0:J, 0:J] G[0:J, J], T_JJ = tau_J.  Lane K's Gram
 // entry is a DPP operand, as in tile_dots; the first block's output stands
@@ -182,7 +211,9 @@ __device__ __forceinline__ void t_column(PanelRegs &pr, int cg) {
     pr.trow[J] = (cg < J) ? -pr.tau * (a0 + a1) : ((cg == J) ? pr.tau : 0.0);
 }
 
-// Steps Q .. 7 or Q .. 15 of panel p (column j = 16 p + Q).  A column past n
+// Steps Q .. 7 or Q .. 15 of panel p (column j = 16 p + Q; Rp: the panel's
+// diagonal block of R, row stride ld; own_w: the wave holds the pivot rows of
+// a first block).  A column past n
 // is zero, and so are its scalars: such a step changes nothing.
 // FIRST: plain QR of the block, whose rows 0 .. n - 1 become R (row j sits
 // in tile 0 of wave p); else the structured QR of [R; block].  With x =
@@ -191,23 +222,25 @@ __device__ __forceinline__ void t_column(PanelRegs &pr, int cg) {
 //     k > j:  w = e_k + s d_k,  c_k -= g w x,  R[j][k] = e_k - g w d,
 //     k = j:  R[j][j] = beta, the column keeps x and its scale s waits,
 //     k < j:  G[k][j] = y_k . y_j = s_k w.
-template <int W, int NS, int NT, bool FIRST, int Q>
+template <int W, int NT, bool FIRST, int Q>
 struct PanelStep {
-    template <typename H>
-    __device__ __forceinline__ static void run(d4 (&c)[NT], PanelRegs &pr, PanelSmem<W, NS, NT> &sm, const int p,
-                                               const int w, const int rg, const int cg, H &hook) {
-        constexpr int LD = PanelSmem<W, NS, NT>::kLd;
+    template <typename SM, typename H>
+    __device__ __forceinline__ static void run(d4 (&c)[NT], PanelRegs &pr, SM &sm, const double *Rp, const int ld,
+                                               const bool own_w, const int w, const int rg, const int cg, H &hook) {
         constexpr int RP = 2 * (Q / 8) + Q % 2;
-        const bool own = FIRST && w == p && rg == (Q % 8) / 2;
+        const bool own = FIRST && own_w && rg == (Q % 8) / 2;
         const double piv = c[0][RP];
         if constexpr (FIRST) c[0][RP] = own ? 0.0 : piv;
         double s4[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int a = 0; a < NT; a += 4) tile_dots<Q>(s4, c[a], c[a + 1], c[a + 2], c[a + 3]);
+        for (int a = 0; a < NT; a += (NT % 4 == 0) ? 4 : 1) {
+            if constexpr (NT % 4 == 0) tile_dots<Q>(s4, c[a], c[a + 1], c[a + 2], c[a + 3]);
+            else tile_dots<Q>(s4, c[a]);
+        }
         double dk = lane_rows_sum((s4[0] + s4[1]) + (s4[2] + s4[3]));
         // R's row j changes only in this step, behind the barrier
         double ek = 0.0;
-        if constexpr (!FIRST) ek = sm.R[(16 * p + Q) * LD + 16 * p + cg];
+        if constexpr (!FIRST) ek = Rp[Q * ld + cg];
         if constexpr (W > 1) {
             constexpr int par = Q & 1;
             if (rg == 0) sm.red[par][16 * w + cg] = dk;
@@ -233,7 +266,10 @@ struct PanelStep {
         const double wv = fma(s, dk, ek);
         const double f = (cg > Q) ? -(g * wv) : 0.0;
 #pragma unroll
-        for (int a = 0; a < NT; a += 2) tile_axpy<Q>(c[a], c[a + 1], f);
+        for (int a = 0; a < NT; a += (NT % 2 == 0) ? 2 : 1) {
+            if constexpr (NT % 2 == 0) tile_axpy<Q>(c[a], c[a + 1], f);
+            else tile_axpy<Q>(c[a], f);
+        }
         if constexpr (FIRST) c[0][RP] = (own && cg < Q) ? piv : c[0][RP];
         {
             // row j of R: kept by the lanes of row Q mod 4 until the panel's end
@@ -247,12 +283,12 @@ struct PanelStep {
         pr.scale = (cg == Q) ? s : pr.scale;
         if constexpr (Q % 8 == 7) t_column<Q>(pr, cg);
         if constexpr (Q + 1 < 16 && Q != 7)
-            PanelStep<W, NS, NT, FIRST, Q + 1>::run(c, pr, sm, p, w, rg, cg, hook);
+            PanelStep<W, NT, FIRST, Q + 1>::run(c, pr, sm, Rp, ld, own_w, w, rg, cg, hook);
     }
 };
 
 // Panel p of panel_qr (below).
-template <int W, int NS, int NT, bool FIRST, bool TRI, typename H, typename F1, typename F2>
+template <int W, int NS, int NT, bool FIRST, typename H, typename F1, typename F2>
 __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const int n, PanelSmem<W, NS, NT> &sm,
                                           const bool want_t, H hook, F1 done, F2 t_block) {
     using SM = PanelSmem<W, NS, NT>;
@@ -262,7 +298,7 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
     double *vt = sm.vt + (NS > 1 ? w * 16 * SM::kVtLd : 0);
     // T[w block, p] from the products P of panel p
     auto t_above = [&](int p) {
-        if constexpr (NS > 1 && W > 1) {
+        if constexpr (NS > 1) {
             if (w < p) {
                 const int cg = lane & 15;
                 d4 acc = d4_zero();
@@ -286,23 +322,18 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
         int cg = lane & 15;
         asm volatile("" : "+v"(cg));   // lane masks are formed in the panel, not kept across it
         PanelRegs pr;
-        pr.scale = 1.0;
-        pr.gq = 0.0;
-        pr.tau = 0.0;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) pr.trow[q] = 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) pr.rrow[u] = 0.0;
+        panel_begin(pr);
         if constexpr (NS > 1) {
 #pragma unroll
             for (int a = 0; a < NT; ++a) settle(c[0][a]);
         }
-        PanelStep<W, NS, NT, FIRST, 0>::run(c[0], pr, sm, p, w, rg, cg, hook);
-        if (nq > 8) PanelStep<W, NS, NT, FIRST, 8>::run(c[0], pr, sm, p, w, rg, cg, hook);
+        double *Rp = sm.R + 16 * p * (LD + 1);   // the panel's diagonal block of R
+        PanelStep<W, NT, FIRST, 0>::run(c[0], pr, sm, Rp, LD, w == p, w, rg, cg, hook);
+        if (nq > 8) PanelStep<W, NT, FIRST, 8>::run(c[0], pr, sm, Rp, LD, w == p, w, rg, cg, hook);
         if (w == 0) {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (cg >= 4 * u + rg) sm.R[(16 * p + 4 * u + rg) * LD + 16 * p + cg] = pr.rrow[u];
+                if (cg >= 4 * u + rg) Rp[(4 * u + rg) * LD + cg] = pr.rrow[u];
         }
         // reflectors: v = s x, and the unit diagonal of a first block
 #pragma unroll
@@ -314,16 +345,15 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
                     if (tile_row(r, rg) == cg && cg < nq) c[0][0][r] = 1.0;
             }
         }
-        double *Tp = (W > 1) ? sm.T + 16 * p * (LD + 1) : sm.T;
-        constexpr int LT = (W > 1) ? LD : 17;
+        double *Tp = sm.T + 16 * p * (LD + 1);   // its diagonal block of T
         if (w == 0 && rg == 0) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) Tp[cg * LT + q] = pr.trow[q];
+            for (int q = 0; q < 16; ++q) Tp[cg * LD + q] = pr.trow[q];
         }
         done(p, c[0], pr.trow);
         if constexpr (NS > 1) {
             const int ntr = np - p;          // slots 1 .. ntr - 1: columns still to update
-            if (p + 1 < np || (W > 1 && want_t)) {
+            if (p + 1 < np || want_t) {
                 // row operands of V
 #pragma unroll
                 for (int a = 0; a < NT; ++a)
@@ -342,10 +372,9 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
                 // V^T C of the columns to update; V_p^T V_t of finished ones
 #pragma unroll
                 for (int s = 1; s < NS; ++s) {
-                    if (s < ntr || (W > 1 && want_t && s >= NS - p)) {
+                    if (s < ntr || (want_t && s >= NS - p)) {
 #pragma unroll
                         for (int a = 0; a < NT; ++a) {
-                            if (TRI && a > p) continue;
 #pragma unroll
                             for (int r = 0; r < 4; ++r) acc[s] = mfma_f64(c[0][a][r], c[s][a][r], acc[s]);
                         }
@@ -369,7 +398,7 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
                                 d4 pg = d4_zero();
 #pragma unroll
                                 for (int kb = 0; kb < 4; ++kb)
-                                    pg = mfma_f64(acc[s][kb], Tp[(4 * kb + rg) * LT + cg], pg);
+                                    pg = mfma_f64(acc[s][kb], Tp[(4 * kb + rg) * LD + cg], pg);
 #pragma unroll
                                 for (int r = 0; r < 4; ++r) sm.P[(16 * w + 4 * r + rg) * 16 + cg] = pg[r];
                             }
@@ -380,7 +409,7 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
                     // M = T^T (R rows + W), -M kept
                     double ta[4];
 #pragma unroll
-                    for (int kb = 0; kb < 4; ++kb) ta[kb] = -Tp[(4 * kb + rg) * LT + cg];
+                    for (int kb = 0; kb < 4; ++kb) ta[kb] = -Tp[(4 * kb + rg) * LD + cg];
                     d4 mm[NS];
 #pragma unroll
                     for (int s = 1; s < NS; ++s) {
@@ -399,7 +428,6 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
                     // C -= V M
 #pragma unroll
                     for (int a = 0; a < NT; ++a) {
-                        if (TRI && a > p) continue;
                         double av[4];
 #pragma unroll
                         for (int kb = 0; kb < 4; ++kb)
@@ -446,15 +474,14 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
 }
 
 // Householder QR of the block c (FIRST) or of [R; c] (R: sm.R).  On exit
-// sm.R is the new triangle and, if want_t, sm.T the block's T (W > 1).
+// sm.R is the new triangle and, if want_t, sm.T the block's T.
 // `hook0` runs in every step of panel 0 while the step waits for LDS, `hook`
 // in every step of the later panels (slot NS - 1 then holds the panel
 // before); a panel of at most 8 columns has steps 0 .. 7 only.
 // `done(p, v, trow)` runs once panel p's reflector columns v (FIRST: with
 // the unit diagonal of the pivot rows written out and zeros above it) and
 // the rows of its T are final, and `t_block(p)` once the columns 16 p ..
-// 16 p + 15 of T are in sm.T (W > 1).  TRI: the block is upper triangular
-// (W = 1: tile a is zero in the columns before 16 a).  PEEL: panel 0 has
+// 16 p + 15 of T are in sm.T. PEEL: panel 0 has
 // code of its own.
 //
 // T above its diagonal blocks comes from the Gram blocks G = V_t^T V_p of the
@@ -462,22 +489,20 @@ __device__ __forceinline__ void panel_one(const int p, d4 (&c)[NS][NT], const in
 // block row t by wave t (the summed Gram block is that wave's left operand
 // as it stands; the products P_t = G_tp T_pp are exchanged through LDS over
 // the barrier that ends the panel).
-template <int W, int NS, int NT, bool FIRST, bool TRI, bool PEEL, typename H0, typename H, typename F1, typename F2>
+template <int W, int NS, int NT, bool FIRST, bool PEEL, typename H0, typename H, typename F1, typename F2>
 __device__ __forceinline__ void panel_qr(d4 (&c)[NS][NT], const int n, PanelSmem<W, NS, NT> &sm, const bool want_t,
                                          H0 hook0, H hook, F1 done, F2 t_block) {
-    static_assert(W == 1 || (W == 4 && NS <= 5), "lane rows sum the waves; a wave per block row of T");
+    static_assert(W == 4 && NS <= W + 1, "lane rows sum the waves; a wave per block row of T");
     const int np = (n + 15) >> 4;
-    if constexpr (PEEL) panel_one<W, NS, NT, FIRST, TRI>(0, c, n, sm, want_t, hook0, done, t_block);
+    if constexpr (PEEL) panel_one<W, NS, NT, FIRST>(0, c, n, sm, want_t, hook0, done, t_block);
     if constexpr (NS > 1 || !PEEL) {
 #pragma unroll 1
         for (int p = PEEL ? 1 : 0; p < np; ++p)
-            panel_one<W, NS, NT, FIRST, TRI>(p, c, n, sm, want_t, hook, done, t_block);
+            panel_one<W, NS, NT, FIRST>(p, c, n, sm, want_t, hook, done, t_block);
     }
-    if constexpr (W > 1) {
-        if (want_t) {
-            __syncthreads();
-            t_block(np - 1);
-        }
+    if (want_t) {
+        __syncthreads();
+        t_block(np - 1);
     }
 }
 
