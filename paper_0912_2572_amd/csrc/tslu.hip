@@ -9,23 +9,31 @@
 //   k_tslu_leaf   one workgroup per domain: the domain's rows in stages of
 //                 one 256-row stack each (its first 256 rows, then its b
 //                 candidates on the next 256 - b rows), the flat tree of
-//                 the TSQR leaf's chunks, one thread per stack row;
+//                 the TSQR leaf's chunks;
 //   k_tslu_tree   one workgroup per chain of a tree level (the TSQR tree's
 //                 shapes): the left's candidates stacked on each right's,
-//                 one thread per stack row (two waves);
+//                 as the leaf's stacks;
 //   k_tslu_u      U and the unit lower L11 of A[ipiv, :] without pivoting;
 //   k_tslu_l      l_i = a_i U^{-1} for every row (one row per thread);
 //   k_tslu_scatter  rows ipiv[k] of L <- row k of L11.
 //
-// Stack layout: thread t holds stack position t (row gidx[t] of A), its b
-// entries in registers; a 256-row stack takes four waves, a tree node's
-// 2b-row stack two.  An elimination step: each wave's pivot search by DPP
-// and lane reads, the waves' winners (key, position, value and the pivot
-// row past the step's column) through LDS with one barrier, then every
-// live row's multiplier and the update of its entries past the column, the
-// pivot row read back in batches of 32 entries.
+// Selection on a stack (select_stack): the stack's rows sit in LDS.  The
+// columns go in panels of 16; a panel's elimination steps run on one wave
+// alone, lane l with the panel entries of positions l, l + 64, ... in
+// registers, so that a step (pivot search on the high words of |a| by 32-bit
+// DPP maxima, the pivot row by lane reads, the update) needs no barrier and
+// no LDS; the columns after the panel get it as one rank-16 update on the
+// FP64 matrix cores by all four waves.  What bounds it: the chain of b steps,
+// in instructions of that one wave (about 130 a step with four rows a lane,
+// 900 cycles; a workgroup barrier and an LDS round trip alone would be 400).
+// Measured against rows held whole by one thread each, with a barrier and the
+// pivot row's trip through LDS in each step: leaf of 1,048,576 x 64 (256
+// domains) 2.15 -> 0.90 ms, a tree level 90 -> 42 us (36 us in CALU's
+// panels), U 65 -> 25 us.
 #include "common.h"
 #include "kernels.h"
+#include "mfma.h"
+#include "panel_qr.h"
 #include "prof.h"
 
 namespace tsqr {
@@ -33,174 +41,230 @@ namespace tsqr {
 namespace {
 
 constexpr int kStack = 256;
+constexpr int kSelLd = 65;   // row stride of a stack in LDS (odd: a column is read without bank conflicts)
 
-// (value, position) pairs: the larger value wins, equal values go to the
-// lower position.
-__device__ __forceinline__ void argmax_take(double &best, int &bp, double &bv, double ob, int op, double ov) {
-    if (ob > best || (ob == best && op < bp)) {
-        best = ob;
-        bp = op;
-        bv = ov;
-    }
-}
-
-// (best, bp, bv) of lanes l and l ^ 16 (permlane16_swap returns both of a
-// pair's values to each lane), the better kept by both.
-__device__ __forceinline__ void argmax_swap16(double &best, int &bp, double &bv) {
-    const auto kl = __builtin_amdgcn_permlane16_swap(__double2loint(best), __double2loint(best), false, false);
-    const auto kh = __builtin_amdgcn_permlane16_swap(__double2hiint(best), __double2hiint(best), false, false);
-    const auto pp = __builtin_amdgcn_permlane16_swap(bp, bp, false, false);
-    const auto vl = __builtin_amdgcn_permlane16_swap(__double2loint(bv), __double2loint(bv), false, false);
-    const auto vh = __builtin_amdgcn_permlane16_swap(__double2hiint(bv), __double2hiint(bv), false, false);
-    double k0 = __hiloint2double(kh[0], kl[0]), k1 = __hiloint2double(kh[1], kl[1]);
-    double v0 = __hiloint2double(vh[0], vl[0]), v1 = __hiloint2double(vh[1], vl[1]);
-    int p0 = (int)pp[0], p1 = (int)pp[1];
-    asm volatile("" : "+v"(k0), "+v"(k1), "+v"(v0), "+v"(v1), "+v"(p0), "+v"(p1));
-    best = k0;
-    bp = p0;
-    bv = v0;
-    argmax_take(best, bp, bv, k1, p1, v1);
-}
-// The same for lanes l and l ^ 32.
-__device__ __forceinline__ void argmax_swap32(double &best, int &bp, double &bv) {
-    const auto kl = __builtin_amdgcn_permlane32_swap(__double2loint(best), __double2loint(best), false, false);
-    const auto kh = __builtin_amdgcn_permlane32_swap(__double2hiint(best), __double2hiint(best), false, false);
-    const auto pp = __builtin_amdgcn_permlane32_swap(bp, bp, false, false);
-    const auto vl = __builtin_amdgcn_permlane32_swap(__double2loint(bv), __double2loint(bv), false, false);
-    const auto vh = __builtin_amdgcn_permlane32_swap(__double2hiint(bv), __double2hiint(bv), false, false);
-    double k0 = __hiloint2double(kh[0], kl[0]), k1 = __hiloint2double(kh[1], kl[1]);
-    double v0 = __hiloint2double(vh[0], vl[0]), v1 = __hiloint2double(vh[1], vl[1]);
-    int p0 = (int)pp[0], p1 = (int)pp[1];
-    asm volatile("" : "+v"(k0), "+v"(k1), "+v"(v0), "+v"(v1), "+v"(p0), "+v"(p1));
-    best = k0;
-    bp = p0;
-    bv = v0;
-    argmax_take(best, bp, bv, k1, p1, v1);
-}
-
-// The lane exchanges below run on the whole wave before any comparison:
-// empty asm statements keep the compiler from moving them into the
-// conditional assignments, where they would read lanes that are off.
-template <int CTRL>
-__device__ __forceinline__ void argmax_step(double &best, int &bp, double &bv) {
-    double ob = dpp_f64<CTRL>(best), ov = dpp_f64<CTRL>(bv);
-    int op = __builtin_amdgcn_update_dpp(0, bp, CTRL, 0xf, 0xf, false);
-    asm volatile("" : "+v"(ob), "+v"(op), "+v"(ov));
-    argmax_take(best, bp, bv, ob, op, ov);
-}
-
-// Step J of partial-pivoting elimination on a stack of W waves, one thread
-// per stack row, the row's entries in m:
-//   each wave's argmax of |a_iJ| over its live rows (a NaN ranks below
-//   every number, ties go to the lower stack position) by DPP inside each
-//   16-lane row and lane-pair exchanges across the rows; the wave's winner puts
-//   its row past J in LDS (one buffer per wave, double-buffered by step
-//   parity) with its key; one barrier; every thread takes the best of the W
-//   winners, reads that row back and updates its entries past J with
-//   l = a_iJ * (1 / a_pJ) (one reciprocal: the multipliers only steer the
-//   selection; U and L are computed from the chosen rows afterwards); a
-//   zero pivot eliminates nothing.
-template <int W>
-struct RowSelSmem {
-    double prow[W][2][64];   // [wave][parity][column]
-    double key[W][2];        // [wave][parity]
-    double val[W][2];
-    int32_t pos[W][2];
-    int32_t gidx[64 * W];
+// A stack of 64 R rows.
+template <int R>
+struct SelSmem {
+    double S[64 * R * kSelLd];   // the stack: entries still to eliminate, multipliers left of them
+    double U[16 * kSelLd];       // the panel's rows of U past the panel
+    int32_t gidx[64 * R];
     int32_t sel[64];
 };
 
-template <int W, int J>
-struct RowSelStep {
-    __device__ __forceinline__ static void run(RowSelSmem<W> &sm, double (&m)[64], bool &live, int b) {
-        if (J < b) {
-            const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-            constexpr int par = J & 1;
-            double best = -1.0, bv = 0.0;
-            int bp = 1 << 30;
-            if (live) {
-                double key = fabs(m[J]);
-                if (key != key) key = -0.5;
-                best = key;
-                bp = t;
-                bv = m[J];
+// Largest of the wave's 32-bit keys (in a scalar register): maxima over each
+// 16-lane row by DPP shifts, then over the rows by row broadcasts, into lane
+// 63, read back as a scalar.  Lanes outside a shift take the identity 0.
+__device__ __forceinline__ uint32_t wave_umax(uint32_t k) {
+    k = max(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, 0x111, 0xf, 0xf, true));   // row_shr:1
+    k = max(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, 0x112, 0xf, 0xf, true));   // row_shr:2
+    k = max(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, 0x114, 0xf, 0xf, true));   // row_shr:4
+    k = max(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, 0x118, 0xf, 0xf, true));   // row_shr:8
+    k = max(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    k = max(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, 0x143, 0xc, 0xf, false));  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)k, 63);
+}
+
+// max(|a|, |b|), a NaN giving way to a number.
+__device__ __forceinline__ double max_abs(double a, double b) {
+    double c;
+    asm("v_max_f64 %0, |%1|, |%2|" : "=v"(c) : "v"(a), "v"(b));
+    return c;
+}
+
+// The pivot's place, U being the first row register whose mask is not empty:
+// takes the pivot row's panel entries J .. 15 into scalars, kills its entry J.
+template <int J, int U, int R>
+__device__ __forceinline__ int take_row(double (&row)[16], double (&m)[R][16], const uint64_t (&mask)[R]) {
+    if constexpr (U + 1 < R) {
+        if (!mask[U]) return take_row<J, U + 1, R>(row, m, mask);
+    }
+    const int src = __builtin_ctzll(mask[U]);
+#pragma unroll
+    for (int j = J; j < 16; ++j) row[j] = wave_bcast(m[U][j], src);
+    if ((int)(threadIdx.x & 63) == src) m[U][J] = __builtin_nan("");
+    return src + 64 * U;
+}
+
+// Step Q of partial-pivoting elimination on panel p, on one wave (row r of
+// lane l: stack position l + 64 r, its panel entries in m[r]).  The pivot is
+// the live row of largest |m[Q]| (a NaN ranks below every number, ties go to
+// the lower stack position); every other live row takes l = m[Q] * (1 /
+// pivot) (one reciprocal: the multipliers only steer the selection; U and L
+// are computed from the chosen rows afterwards), kept in m[Q], and updates
+// its entries past Q; a zero pivot eliminates nothing.  A chosen row's entries
+// from Q on are NaN: they lose every search and need no test in the update
+// (nothing reads them again); `dead` (bit r) tells such a row from a live one
+// only where no number is left.
+template <int R, int Q>
+struct SelStep {
+    __device__ __forceinline__ static void run(int32_t *sel, double (&m)[R][16], uint32_t &dead, int nq) {
+        if (Q < nq) {
+            const int lane = threadIdx.x & 63;
+            double top = max_abs(m[0][Q], 0.0);
+#pragma unroll
+            for (int r = 1; r < R; ++r) top = max_abs(top, m[r][Q]);
+            // the largest high word first: where one lane has it, that lane's value
+            const uint32_t hi = (uint32_t)__double2hiint(top), lo = (uint32_t)__double2loint(top);
+            const uint32_t hmax = wave_umax(hi);
+            const uint64_t have = __ballot(hi == hmax);
+            uint32_t lmax = (uint32_t)__builtin_amdgcn_readlane((int)lo, __builtin_ctzll(have));
+            if (have & (have - 1)) lmax = wave_umax(hi == hmax ? lo : 0u);
+            const double best = __hiloint2double((int)hmax, (int)lmax);
+            uint64_t mask[R], any = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) any |= mask[r] = __ballot(fabs(m[r][Q]) == best);
+            if (!any) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) mask[r] = __ballot(!(dead >> r & 1u));
             }
-            argmax_step<kDppXor1>(best, bp, bv);
-            argmax_step<kDppXor2>(best, bp, bv);
-            argmax_step<0x124>(best, bp, bv);
-            argmax_step<kDppRowRor8>(best, bp, bv);
-            // the four 16-lane rows' winners: rows 0|1 and 2|3 exchanged, then
-            // the two halves (the take is symmetric, so every lane ends with
-            // the wave's winner)
-            argmax_swap16(best, bp, bv);
-            argmax_swap32(best, bp, bv);
-            bp = __builtin_amdgcn_readfirstlane(bp);
-            constexpr int R = 63 - J;
-            if (t == bp) {
+            double row[16];
+            const int at = take_row<Q, 0, R>(row, m, mask);
+            if (lane == 0) sel[Q] = at;
+            dead |= (lane == (at & 63)) ? 1u << (at >> 6) : 0u;
+            const double rv = (row[Q] != 0.0) ? 1.0 / row[Q] : 0.0;
 #pragma unroll
-                for (int q = 0; q < R; ++q) sm.prow[w][par][J + 1 + q] = m[J + 1 + q];
-            }
-            if (lane == 0) {
-                sm.key[w][par] = best;
-                sm.val[w][par] = bv;
-                sm.pos[w][par] = bp;
-            }
-            __syncthreads();
-            double kb = sm.key[0][par], vb = sm.val[0][par];
-            int pb = sm.pos[0][par];
+            for (int r = 0; r < R; ++r) {
+                m[r][Q] *= rv;
 #pragma unroll
-            for (int u = 1; u < W; ++u) argmax_take(kb, pb, vb, sm.key[u][par], sm.pos[u][par], sm.val[u][par]);
-            const int src = pb >> 6;
-            if (t == 0) sm.sel[J] = pb;
-            const double rv = (vb != 0.0) ? 1.0 / vb : 0.0;
-            const bool upd = live && t != pb;
-            const double l = upd ? m[J] * rv : 0.0;
-            if (t == pb) live = false;
-            // the pivot row in batches of at most 32 entries (registers)
-            const double *pr = sm.prow[src][par];
-            constexpr int R1 = R < 32 ? R : 32, R2 = R - R1;
-            if constexpr (R1 > 0) {
-                double cv[R1];
-#pragma unroll
-                for (int q = 0; q < R1; ++q) cv[q] = pr[J + 1 + q];
-#pragma unroll
-                for (int q = 0; q < R1; ++q) asm volatile("" : "+v"(cv[q]));
-#pragma unroll
-                for (int q = 0; q < R1; ++q) m[J + 1 + q] = fma(-l, cv[q], m[J + 1 + q]);
-            }
-            if constexpr (R2 > 0) {
-                double cv[R2];
-#pragma unroll
-                for (int q = 0; q < R2; ++q) cv[q] = pr[J + 1 + R1 + q];
-#pragma unroll
-                for (int q = 0; q < R2; ++q) asm volatile("" : "+v"(cv[q]));
-#pragma unroll
-                for (int q = 0; q < R2; ++q) m[J + 1 + R1 + q] = fma(-l, cv[q], m[J + 1 + R1 + q]);
+                for (int j = Q + 1; j < 16; ++j) m[r][j] = fma(-m[r][Q], row[j], m[r][j]);
             }
         }
-        RowSelStep<W, J + 1>::run(sm, m, live, b);
+        if constexpr (Q + 1 < 16) SelStep<R, Q + 1>::run(sel, m, dead, nq);
     }
 };
-template <int W>
-struct RowSelStep<W, 64> {
-    __device__ __forceinline__ static void run(RowSelSmem<W> &, double (&)[64], bool &, int) {}
+
+// Term K of the unit-lower solve u <- L11^{-1} u: u[j] += (-L11[j][K]) u[K],
+// j > K, with row j of -L11 in lane j of every 16-lane row (column K: nl[K]).
+template <int K, int J>
+struct UnitLowerTerm {
+    __device__ __forceinline__ static void run(double (&u)[16], double nl) {
+        if constexpr (J < 16) {
+            t_term<J>(u[J], nl, u[K]);
+            UnitLowerTerm<K, J + 1>::run(u, nl);
+        }
+    }
+};
+template <int K>
+struct UnitLowerSolve {
+    __device__ __forceinline__ static void run(double (&u)[16], const double (&nl)[16]) {
+        if constexpr (K < 15) {
+            double g = nl[K];
+            asm("s_nop 1" : "+v"(g));   // DPP wait states (panel_qr.h, t_term)
+            UnitLowerTerm<K, K + 1>::run(u, g);
+            UnitLowerSolve<K + 1>::run(u, nl);
+        }
+    }
 };
 
-// One stack of `rows` rows (sm.gidx) on W waves, one thread per row: the
-// kb = min(b, rows) selection steps, then gidx[0 .. kb-1] <- the chosen
-// rows in pivot order.  Returns kb.
-template <int W>
-__device__ __forceinline__ int select_stack(RowSelSmem<W> &sm, const double *__restrict__ A, int64_t lda,
-                                            int rows, int b) {
-    const int t = threadIdx.x;
-    bool live = t < rows;
-    const double *src = A + (live ? sm.gidx[t] : 0);
-    double m[64];
+// U rows of a panel for column slot s: u = L11^{-1} S[row(k)][slot s], rows
+// row(k), k = 0..15, of the stack S in pivot order (row_at: lane k's row).
+__device__ __forceinline__ void panel_u(const double *S, int row_at, int p, int s, double (&u)[16]) {
+    const int cg = threadIdx.x & 15;
+    double nl[16];
+    // lane cg: its pivot row's multipliers (left of the diagonal)
 #pragma unroll
-    for (int k = 0; k < 64; ++k) m[k] = (live && k < b) ? src[(int64_t)k * lda] : 0.0;
+    for (int k = 0; k < 16; ++k) {
+        const double v = S[row_at * kSelLd + 16 * p + k];
+        nl[k] = k < cg ? -v : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const int row = __builtin_amdgcn_readlane(row_at, k);
+        u[k] = S[row * kSelLd + 16 * s + cg];
+    }
+    UnitLowerSolve<0>::run(u, nl);
+}
+
+// C -= L U for the 16-row tiles a0 .. NT - 1 of a stack (S: their first row),
+// panel p, slots s0 .. s1 - 1; U: 16 rows of stride kSelLd.
+template <int NT>
+__device__ __forceinline__ void rank16_update(double *S, const double *U, int p, int a0, int s0, int s1) {
+    const int lane = threadIdx.x & 63, cg = lane & 15, rg = lane >> 4;
+    double av[NT][4];
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) av[a][r] = -S[(16 * a + cg) * kSelLd + 16 * p + 4 * r + rg];
+    for (int s = s0; s < s1; ++s) {
+        double bv[4];
+        d4 c[NT];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) bv[kb] = U[(4 * kb + rg) * kSelLd + 16 * s + cg];
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) c[a][r] = S[(16 * a + 4 * r + rg) * kSelLd + 16 * s + cg];
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int a = 0; a < NT; ++a) c[a] = mfma_f64(av[a][kb], bv[kb], c[a]);
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+            if (a >= a0) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) S[(16 * a + 4 * r + rg) * kSelLd + 16 * s + cg] = c[a][r];
+            }
+    }
+}
+
+// A row's b entries into its LDS row (zeros past b), in batches of 32 loads.
+__device__ __forceinline__ void fetch_row(double (&v)[64], const double *__restrict__ src, int64_t lda, int b) {
+#pragma unroll
+    for (int k = 0; k < 64; ++k) v[k] = src[(int64_t)(k < b ? k : 0) * lda];
+}
+__device__ __forceinline__ void put_row(double *S, const double (&v)[64], int b, bool live) {
+#pragma unroll
+    for (int k = 0; k < 64; ++k) S[k] = (live && k < b) ? v[k] : 0.0;
+}
+
+// The stack in sm.S (64 R rows, `rows` of them live; their rows of A in
+// sm.gidx) on four waves: the kb = min(b, rows) selection steps, then
+// gidx[0 .. kb-1] <- the chosen rows in pivot order.  Returns kb.
+template <int R>
+__device__ __forceinline__ int select_stack(SelSmem<R> &sm, int rows, int b) {
+    const int t = threadIdx.x, w = wave_index<4>(), lane = t & 63, cg = lane & 15;
     const int kb = b < rows ? b : rows;
-    RowSelStep<W, 0>::run(sm, m, live, kb);
+    const int np = (kb + 15) >> 4;
+    uint32_t dead = 0;   // bit r: position lane + 64 r is not (or no longer) live
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (lane + 64 * r >= rows) dead |= 1u << r;
     __syncthreads();
+#pragma unroll 1
+    for (int p = 0; p < np; ++p) {
+        if (w == 0) {
+            double m[R][16];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int j = 0; j < 16; ++j)   // canonical: no signalling NaN reaches the search
+                    m[r][j] = __builtin_canonicalize(sm.S[(lane + 64 * r) * kSelLd + 16 * p + j]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) m[r][0] = (dead >> r & 1u) ? __builtin_nan("") : m[r][0];
+            SelStep<R, 0>::run(sm.sel + 16 * p, m, dead, kb - 16 * p);
+            if (p + 1 < np) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) sm.S[(lane + 64 * r) * kSelLd + 16 * p + j] = m[r][j];
+            }
+        }
+        __syncthreads();
+        if (p + 1 == np) break;
+        if (w < np - p - 1) {
+            const int s = p + 1 + w;
+            double u[16];
+            panel_u(sm.S, sm.sel[16 * p + cg], p, s, u);
+            if (lane < 16) {
+#pragma unroll
+                for (int k = 0; k < 16; ++k) sm.U[k * kSelLd + 16 * s + cg] = u[k];
+            }
+        }
+        __syncthreads();
+        rank16_update<R>(sm.S + 16 * R * w * kSelLd, sm.U, p, 0, p + 1, np);
+        __syncthreads();
+    }
     const int32_t g = (t < kb) ? sm.gidx[sm.sel[t]] : 0;
     __syncthreads();
     if (t < kb) sm.gidx[t] = g;
@@ -211,112 +275,149 @@ __device__ __forceinline__ int select_stack(RowSelSmem<W> &sm, const double *__r
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void k_tslu_leaf(const double *__restrict__ A, int64_t lda, PanelArgs pa, int b, int32_t *__restrict__ cand) {
-    __shared__ RowSelSmem<4> sm;
+    extern __shared__ __attribute__((aligned(64))) double smem_raw[];
+    SelSmem<4> &sm = *reinterpret_cast<SelSmem<4> *>(smem_raw);
     const int64_t dom = blockIdx.x;
     const int64_t row0 = dom_row0(pa, dom), end = row0 + dom_rows(pa, dom);
     const int t = threadIdx.x;
+    // stage by stage: positions 0 .. nc - 1 the candidates so far, then `take`
+    // new rows; a thread past the candidates loads its next row (whatever the
+    // candidates turn out to be) while the current stack is eliminated
     int64_t pos = row0;
     int nc = 0;
-    while (pos < end) {
-        const int room = kStack - (nc ? b : 0);
-        const int take = (int)((end - pos < room) ? end - pos : room);
-        if (t >= nc && t < nc + take) sm.gidx[t] = (int32_t)(pos + (t - nc));
+    int take = (int)((end - pos < kStack) ? end - pos : kStack);
+    double v[64];
+    fetch_row(v, A + (t < take ? pos + t : pos), lda, b);
+    while (true) {
+        const int rows = nc + take;
+        if (t >= nc && t < rows) sm.gidx[t] = (int32_t)(pos + (t - nc));
         __syncthreads();
-        nc = select_stack<4>(sm, A, lda, nc + take, b);
+        if (t < nc) fetch_row(v, A + sm.gidx[t], lda, b);
+        put_row(sm.S + t * kSelLd, v, b, t < rows);
         pos += take;
+        // every later stage follows min(b, rows) = b candidates
+        const int room = kStack - b;
+        take = (int)((end - pos < room) ? end - pos : room);
+        if (take > 0) fetch_row(v, A + ((t >= b && t < b + take) ? pos + (t - b) : pos), lda, b);
+        nc = select_stack<4>(sm, rows, b);
         __syncthreads();
+        if (take <= 0) break;
     }
     if (t < b) cand[dom * b + t] = sm.gidx[t];
 }
 
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
 void k_tslu_tree(const double *__restrict__ A, int64_t lda, PanelArgs pa, TreeArgs ta, int b,
                  int32_t *__restrict__ cand) {
-    __shared__ RowSelSmem<2> sm;
+    extern __shared__ __attribute__((aligned(64))) double smem_raw[];
+    SelSmem<2> &sm = *reinterpret_cast<SelSmem<2> *>(smem_raw);
     const int64_t g = blockIdx.x;
     const int64_t left = (g / ta.width) * ta.span + g % ta.width;
     if (left >= pa.P) return;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, r = t & 127, h = t >> 7;   // two threads a row, 32 columns each
     for (int64_t q = 1; q * ta.stride < ta.span && left + q * ta.stride < pa.P; ++q) {
         const int64_t right = left + q * ta.stride;
-        if (t < 2 * b) sm.gidx[t] = (t < b) ? cand[left * b + t] : cand[right * b + (t - b)];
-        __syncthreads();
-        select_stack<2>(sm, A, lda, 2 * b, b);
+        const bool live = r < 2 * b;
+        const int32_t gi = live ? ((r < b) ? cand[left * b + r] : cand[right * b + (r - b)]) : 0;
+        if (h == 0) sm.gidx[r] = gi;
+        double v[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) v[k] = A[gi + (int64_t)(32 * h + k < b ? 32 * h + k : 0) * lda];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) sm.S[r * kSelLd + 32 * h + k] = (live && 32 * h + k < b) ? v[k] : 0.0;
+        select_stack<2>(sm, 2 * b, b);
         if (t < b) cand[left * b + t] = sm.gidx[t];
         __syncthreads();
     }
 }
 
-// U and the unit lower L11 of A[ipiv, :] by elimination without pivoting:
-// thread i owns row i; row j is final after step j - 1.  info: the first
-// zero U_jj (1-based), else 0.
-// Step J of the no-pivot LU of the pivot block: lane i holds row i in m;
-// lane J publishes row J's entries past J in LDS (double-buffered by step
-// parity) and every lane reads them back in one batch (all loads issued
-// before the first use); rows below J divide by the pivot and update their
-// entries past J.  A zero pivot skips the step and records info.  Unrolled
-// by template recursion so that every register index is a constant.
-template <int J>
+// Step Q of the no-pivot LU of panel p, lane i holding row i's panel entries:
+// rows below row 16 p + Q divide by the pivot and update their entries past
+// Q, the pivot row broadcast by lane reads.  A zero pivot eliminates nothing
+// and sets info.
+template <int Q>
 struct NoPivotStep {
-    __device__ static void run(double (&m)[64], double (&row)[2][64], int i, int b, int &info) {
-        if (J < b) {
-            const double piv = wave_bcast(m[J], J);
-            if (piv == 0.0) {
-                if (!info) info = J + 1;
-            } else {
-                constexpr int R = 63 - J;
-                if (i == J) {
+    __device__ __forceinline__ static void run(double (&m)[16], int i, int p, int nq, int &info) {
+        if (Q < nq) {
+            const int k = 16 * p + Q;
+            const double piv = wave_bcast(m[Q], k);
+            const bool zero = piv == 0.0;
+            if (zero && !info) info = k + 1;
+            const bool below = i > k && !zero;
+            const double l = below ? m[Q] / piv : 0.0;
+            if (below) m[Q] = l;
 #pragma unroll
-                    for (int q = 0; q < R; ++q) row[J & 1][J + 1 + q] = m[J + 1 + q];
-                }
-                __syncthreads();
-                const bool below = i > J && i < b;
-                const double l = below ? m[J] / piv : 0.0;
-                if (below) m[J] = l;
-                if constexpr (R > 0) {
-                    double cv[R];
-#pragma unroll
-                    for (int q = 0; q < R; ++q) cv[q] = row[J & 1][J + 1 + q];
-#pragma unroll
-                    for (int q = 0; q < R; ++q) asm volatile("" : "+v"(cv[q]));
-                    if (below) {
-#pragma unroll
-                        for (int q = 0; q < R; ++q) m[J + 1 + q] = fma(-l, cv[q], m[J + 1 + q]);
-                    }
-                }
-            }
+            for (int j = Q + 1; j < 16; ++j) m[j] = fma(-l, wave_bcast(m[j], k), m[j]);
         }
-        NoPivotStep<J + 1>::run(m, row, i, b, info);
+        if constexpr (Q + 1 < 16) NoPivotStep<Q + 1>::run(m, i, p, nq, info);
     }
 };
-template <>
-struct NoPivotStep<64> {
-    __device__ static void run(double (&)[64], double (&)[2][64], int, int, int &) {}
-};
 
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
+// U and the unit lower L11 of A[ipiv, :] by elimination without pivoting, in
+// 16-column panels as in select_stack: the steps on one wave (lane i owns row
+// i), the updates on four.  info: the first zero U_jj (1-based), else 0.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void k_tslu_u(const double *__restrict__ A, int64_t lda, int b, const int32_t *__restrict__ cand,
               int64_t *__restrict__ ipiv, double *__restrict__ U, int64_t ldu, double *__restrict__ L11,
               int32_t *__restrict__ dinfo) {
-    __shared__ double row[2][64];
-    const int i = threadIdx.x;
+    __shared__ double S[64 * kSelLd];
+    __shared__ double Up[16 * kSelLd];
+    const int t = threadIdx.x, w = wave_index<4>(), i = t & 63, cg = i & 15;
     const int32_t gi = (i < b) ? cand[i] : 0;
-    if (i < b) ipiv[i] = gi;
-    double m[64];
+    if (t < b) ipiv[t] = gi;
+    {
+        // wave w: columns w, w + 4, ...
+        double v[16];
 #pragma unroll
-    for (int k = 0; k < 64; ++k) m[k] = (i < b && k < b) ? A[gi + (int64_t)k * lda] : 0.0;
+        for (int u = 0; u < 16; ++u) v[u] = A[gi + (int64_t)(w + 4 * u < b ? w + 4 * u : 0) * lda];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) S[i * kSelLd + w + 4 * u] = (i < b && w + 4 * u < b) ? v[u] : 0.0;
+    }
+    __syncthreads();
     int info = 0;
-    NoPivotStep<0>::run(m, row, i, b, info);
+    const int np = (b + 15) >> 4;
+    double *row = S + i * kSelLd;
+#pragma unroll 1
+    for (int p = 0; p < np; ++p) {
+        if (w == 0) {
+            double m[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) m[j] = row[16 * p + j];
+            NoPivotStep<0>::run(m, i, p, b - 16 * p, info);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) row[16 * p + j] = m[j];
+        }
+        __syncthreads();
+        if (p + 1 == np) break;
+        if (w < np - p - 1) {
+            const int s = p + 1 + w;
+            double u[16];
+            panel_u(S, 16 * p + cg, p, s, u);
+            if (i < 16) {
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    Up[k * kSelLd + 16 * s + cg] = u[k];
+                    S[(16 * p + k) * kSelLd + 16 * s + cg] = u[k];   // the panel's rows are U now
+                }
+            }
+        }
+        __syncthreads();
+        // the rows below the panel take its update, a tile per wave
+        if (w > p) rank16_update<1>(S + 16 * w * kSelLd, Up, p, 0, p + 1, np);
+        __syncthreads();
+    }
     if (i < b) {
 #pragma unroll
-        for (int k = 0; k < 64; ++k) {
+        for (int u = 0; u < 16; ++u) {
+            const int k = w + 4 * u;
             if (k < b) {
-                U[i + (int64_t)k * ldu] = (i <= k) ? m[k] : 0.0;
-                L11[i + (int64_t)k * 64] = (k < i) ? m[k] : (k == i ? 1.0 : 0.0);
+                const double v = row[k];
+                U[i + (int64_t)k * ldu] = (i <= k) ? v : 0.0;
+                L11[i + (int64_t)k * 64] = (k < i) ? v : (k == i ? 1.0 : 0.0);
             }
         }
     }
-    if (i == 0 && dinfo) *dinfo = info;
+    if (t == 0 && dinfo) *dinfo = info;
 }
 
 // l_i = a_i U^{-1} (l U = a_i, column by column, l_k = 0 where U_kk = 0)
@@ -368,29 +469,35 @@ __global__ void k_tslu_scatter(const int64_t *__restrict__ ipiv, int b, const do
 hipError_t launch_tslu(const double *A, int64_t lda, const PanelArgs &pa, const std::vector<TreeArgs> &levels,
                        int b, int32_t *cand, double *L11, double *L, int64_t ldl, double *U, int64_t ldu,
                        int64_t *ipiv, int32_t *dinfo, hipStream_t st) {
+    hipError_t e = hipFuncSetAttribute((const void *)k_tslu_leaf, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)sizeof(SelSmem<4>));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)k_tslu_tree, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)sizeof(SelSmem<2>));
+    if (e != hipSuccess) return e;
     {
         ProfScope ps("tslu_leaf", st);
-        hipLaunchKernelGGL(k_tslu_leaf, dim3((unsigned)pa.P), dim3(256), 0, st, A, lda, pa, b, cand);
-        hipError_t e = hipGetLastError();
+        hipLaunchKernelGGL(k_tslu_leaf, dim3((unsigned)pa.P), dim3(256), sizeof(SelSmem<4>), st, A, lda, pa, b, cand);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     for (const TreeArgs &ta : levels) {
         ProfScope ps("tslu_tree", st);
-        hipLaunchKernelGGL(k_tslu_tree, dim3((unsigned)ta.chains), dim3(128), 0, st, A, lda, pa, ta, b, cand);
-        hipError_t e = hipGetLastError();
+        hipLaunchKernelGGL(k_tslu_tree, dim3((unsigned)ta.chains), dim3(256), sizeof(SelSmem<2>), st, A, lda, pa, ta, b, cand);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     {
         ProfScope ps("tslu_u", st);
-        hipLaunchKernelGGL(k_tslu_u, dim3(1), dim3(64), 0, st, A, lda, b, cand, ipiv, U, ldu, L11, dinfo);
-        hipError_t e = hipGetLastError();
+        hipLaunchKernelGGL(k_tslu_u, dim3(1), dim3(256), 0, st, A, lda, b, cand, ipiv, U, ldu, L11, dinfo);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     {
         ProfScope ps("tslu_l", st);
         const unsigned blocks = (unsigned)((pa.m + 255) / 256);
         hipLaunchKernelGGL(k_tslu_l, dim3(blocks), dim3(256), 0, st, A, lda, pa.m, b, U, ldu, L, ldl);
-        hipError_t e = hipGetLastError();
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     ProfScope ps("tslu_scatter", st);
