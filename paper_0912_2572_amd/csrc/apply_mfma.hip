@@ -1,6 +1,7 @@
-// apply_mfma.hip -- leaf part of Q^T B / Q B on matrix cores, for blocks of
-// up to 16 columns of B (least squares, refinement corrections, and the
-// trailing update between 64-column panels).
+// apply_mfma.hip -- leaf part of Q^T B / Q B on matrix cores: a chained form
+// for blocks of 16 or 32 columns of B (the trailing update between 64-column
+// panels, many right-hand sides) and a three-pass form for up to 16 columns
+// (least squares, refinement corrections).
 //
 // Per chunk of a domain (compact-WY factor I - Y T Y^T, Sec. 2.2):
 //     W = Yb + V^T B_c          (Yb = the domain's top n rows; 0 on a first
@@ -9,9 +10,7 @@
 //     Yb -= Z,   B_c -= V Z
 // W is reduced over the chunk's rows by 16x16x4 MFMA tiles with the row index
 // as the reduction dimension (each wave takes a quarter of the rows, the
-// four partials meet in LDS); the update runs transposed,
-// (B_c - V Z)^T = B_c^T - Z^T V^T, so that each store writes 16 consecutive
-// rows of a column.
+// four partials meet in LDS).
 //
 // Two precisions share the code: FP64 (V in FP64, v_mfma_f64_16x16x4f64) and
 // the mixed mode's FP32 path (V stored in FP32, v_mfma_f32_16x16x4f32 with
@@ -19,23 +18,17 @@
 // FP64, and B is updated as B - (V Z) with only the product in the tile
 // precision, so an FP32 apply perturbs B by about u32 times the size of the
 // update rather than u32 times |B|.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "mfma.h"
+#include "panel_qr.h"
 #include "prof.h"
 
 namespace tsqr {
 
-constexpr int KBM = 16;   // columns of B per workgroup
-
-template <typename Tile>
-struct ApplyMSmem {
-    using T = typename Tile::T;
-    T Tm[64 * kLdsStride];
-    T Wp[4][64][KBM];   // per-wave partials of W; then W in Wp[1] and Z in Wp[0]
-    double Y[64][KBM];  // the domain's top n rows of B (columns of this block)
-};
-static_assert(2 * sizeof(ApplyMSmem<TileF64>) <= 160 * 1024, "two workgroups per CU");
+constexpr int KBM = 16;   // most columns of B of the three-pass form
 
 // V element of a chunk with the implicit unit diagonal of a first chunk.
 template <typename VT>
@@ -74,212 +67,470 @@ __device__ __forceinline__ bool wide_rows_ok(const VT *v, int64_t ldv, const dou
            (ldb * 8) % 16 == 0;
 }
 
+// ---------------------------------------------------------------------------
+// Chained leaf apply: one workgroup per domain and block of 16 NB columns walks
+// the domain's chunks.  A wave owns a quarter of each chunk's rows.  Its rows of
+// V and B come from memory once, a column per load (lane = row: 512 consecutive
+// bytes; the operand layouts' own order would touch a cache line per lane, and
+// the address unit then bounds the kernel), the next chunk's loads in flight
+// while the current chunk is processed, and pass to the matrix cores' layouts
+// through the wave's own part of LDS (no barrier):
+//   W:  V^T B over the wave's rows; the waves' partials meet in LDS, wave w
+//       summing reflectors 16 w .. 16 w + 15 and adding its rows of Yb (in
+//       registers for the whole chain);
+//   Z:  op(T) W, the same rows per wave;
+//   B:  B - V Z in tiles whose accumulators are B's, stored by columns again.
+// What bounds it: per chunk of 256 rows, n = 64 and 32 columns, 16.4 thousand
+// cycles of FP64 tiles on each of a compute unit's four waves, of about 30
+// thousand (the rest are the LDS passes and the seven barriers of W and Z),
+// with 256 KB of loads and stores.  Measured against one 16-column block per
+// workgroup with both operands read from memory in their own layouts and
+// nothing in flight between phases: trailing updates of 131,072 x 512 (7
+// launches, 448 .. 64 columns) 5.03 -> 2.41 ms; Q^T B and Q B of 300,001 x 40,
+// 24 columns, 0.54 -> 0.146 ms each; FP32 reflectors, 1,048,576 x 64 on 64
+// columns, 0.58 -> 0.26 ms.
+
+// Row of a 16-row tile of B (in load order) that row i of a product tile is.
 template <typename Tile>
-__device__ __forceinline__ void chunk_apply_m(ApplyMSmem<Tile> &sm, const typename Tile::T *__restrict__ Vc, int64_t ldv,
-                              const double *__restrict__ Tk, const double *__restrict__ Bin, int64_t ldbi,
-                              double *__restrict__ Bout, int64_t ldbo, int64_t valid, int n, int kc,
-                              bool first, int trans) {
+__device__ __forceinline__ int tile_row_of(int i) {
+    if constexpr (sizeof(typename Tile::T) == 8) return 4 * (i & 3) + (i >> 2);
+    else return i;
+}
+
+// Place of row r in column c of a wave's part: the 16-byte pieces of a column
+// are permuted by the column (exclusive or on the low four bits), so that 16
+// columns at one row, and the 16 rows of a tile in neighbouring columns, fall
+// into different banks.
+template <typename T>
+__device__ __forceinline__ int row_place(int r, int c) {
+    if constexpr (sizeof(T) == 8) return r ^ (2 * (((c & 1) << 3) | ((c >> 1) & 7)));
+    else return r ^ (4 * (((c & 3) << 2) | ((c >> 2) & 3)));
+}
+
+template <typename Tile, int NT, int NB>
+struct LeafApplySmem {
+    using T = typename Tile::T;
+    static constexpr int RT = NT == 1 ? 8 : 4;   // 16-row tiles of a wave (chunk_rows)
+    T V[4][16 * NT][16 * RT];                    // [wave][reflector][row_place]
+    // in turn: per wave 16 columns of B; the partials of W that cross waves,
+    // W, Z; Yb's exchange
+    alignas(64) unsigned char x[4 * 16 * 16 * RT * sizeof(double)];
+    static_assert(sizeof(x) >= 3 * NT * 64 * sizeof(typename Tile::Acc) &&
+                      sizeof(x) >= 16 * NT * 16 * NB * sizeof(double), "every use fits");
+};
+static_assert(sizeof(LeafApplySmem<TileF64, 4, 2>) <= 160 * 1024, "fits a CU's LDS");
+
+// The work of one chain: domain `dom`, columns c0 .. c0 + kc - 1, in groups of
+// 8 domains x ncb column blocks, the column blocks of one domain 8 items
+// apart.  Workgroup g takes items g, g + gridDim.x, ... (a multiple of 8), and
+// workgroups go to the 8 XCDs round-robin by index: a domain's column blocks
+// share one XCD (one L2) and run side by side, so that its V comes from HBM
+// about once instead of ncb times.
+struct ApplyItem {
+    int64_t dom, row0, nrows, nch, c0;
+    int kc;
+};
+template <int NB>
+__device__ __forceinline__ bool apply_item(const PanelArgs &pa, int64_t k, int ncb, int64_t g, ApplyItem &it) {
+    const int64_t per = 8 * (int64_t)ncb, within = g % per;
+    it.dom = (g / per) * 8 + within % 8;
+    if (it.dom >= pa.P) return false;
+    it.c0 = within / 8 * (16 * NB);
+    it.kc = (int)((k - it.c0 < 16 * NB) ? k - it.c0 : 16 * NB);
+    it.row0 = dom_row0(pa, it.dom);
+    it.nrows = dom_rows(pa, it.dom);
+    it.nch = (it.nrows + pa.chunk - 1) / pa.chunk;
+    return true;
+}
+
+template <typename Tile, int NT, int NB, bool QT>
+__device__ __forceinline__ void leaf_apply_chains(LeafApplySmem<Tile, NT, NB> &sm,
+                                                  const typename Tile::T *__restrict__ Vp, int64_t ldv,
+                                                  const double *__restrict__ Tc, const PanelArgs &pa,
+                                                  const double *Bsrcp, int64_t ldbs, double *Bp, int64_t ldb,
+                                                  int64_t k, int ncb) {
     using T = typename Tile::T;
     using Acc = typename Tile::Acc;
-    const int tid = local_tid(), lane = tid & 63, w = tid >> 6;
-    const int l16 = lane & 15, l4 = lane >> 4;
-    const int mtn = (n + 15) >> 4;             // 16-reflector tiles
-    for (int e = tid; e < 64 * 64; e += 256) {
-        const int r = e & 63, q = e >> 6;
-        sm.Tm[r * kLdsStride + q] = (r < n && q < n) ? T(Tk[r + (int64_t)q * n]) : T(0);
-    }
-    // W partial over this wave's rows: W[m][j] += sum_r V[r][m] B[r][j]
-    {
-        Acc acc[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[mt] = Acc{0, 0, 0, 0};
-        const int64_t per = ((valid + 15) / 16 + 3) / 4 * 16;   // rows per wave, multiple of 16
-        const int64_t lo = w * per, hi = (lo + per < valid) ? lo + per : valid;
-        if (!first && wide_rows_ok(Vc + lo, ldv, Bin + lo, ldbi, hi - lo)) {
-            // 16-byte loads of 4 consecutive rows per lane (as in the first pass)
-#pragma unroll 1
-            for (int64_t r16 = lo; r16 < hi; r16 += 16) {
-                const int64_t rb = r16 + 4 * l4;
-                T b4[4];
-                load4<T>(Bin + rb + (int64_t)l16 * ldbi, l16 < kc, b4);
-#pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
-                    if (mt >= mtn) break;
-                    T a4[4];
-                    load4<T>(Vc + rb + (int64_t)(16 * mt + l16) * ldv, 16 * mt + l16 < n, a4);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[mt] = Tile::mfma(a4[q], b4[q], acc[mt]);
-                }
-            }
-        } else {
-            for (int64_t r4 = lo; r4 < hi; r4 += 4) {
-                const int64_t row = r4 + l4;
-                double bv = 0.0;
-                if (row < hi && l16 < kc) {
-                    if (first && !trans && row < n) bv = sm.Y[row][l16];
-                    else bv = Bin[row + (int64_t)l16 * ldbi];
-                }
-                const T b = T(bv);
-#pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
-                    if (mt >= mtn) break;
-                    const T a = (row < hi) ? v_elem<T>(Vc, ldv, row, 16 * mt + l16, valid, n, first) : T(0);
-                    acc[mt] = Tile::mfma(a, b, acc[mt]);
-                }
-            }
-        }
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sm.Wp[w][16 * mt + Tile::drow(r, lane)][l16] = acc[mt][r];
-    }
-    __syncthreads();
-    for (int e = tid; e < 64 * KBM; e += 256) {
-        const int m = e >> 4, j = e & 15;
-        T s = ((sm.Wp[0][m][j] + sm.Wp[1][m][j]) + sm.Wp[2][m][j]) + sm.Wp[3][m][j];
-        if (!first) s += T(sm.Y[m][j]);
-        sm.Wp[1][m][j] = s;   // W: each entry read and written by one thread
-    }
-    __syncthreads();
-    // Z = op(T) W (W in Wp[1]) on the matrix cores, written over the
-    // partial buffer of wave 0: wave w computes rows 16 w .. 16 w + 15 (T is
-    // zero outside its upper triangle and past n, so the full 64-wide sum is
-    // op(T) W; W rows past n are not formed and enter as zeros)
-    {
-        Acc acc = Acc{0, 0, 0, 0};
-        const int i = 16 * w + l16;
-#pragma unroll
-        for (int kb = 0; kb < 16; ++kb) {
-            if (4 * kb >= n) break;
-            const int q = 4 * kb + l4;
-            const T a = trans ? sm.Tm[q * kLdsStride + i] : sm.Tm[i * kLdsStride + q];
-            const T b = (q < n) ? sm.Wp[1][q][l16] : T(0);
-            acc = Tile::mfma(a, b, acc);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sm.Wp[0][16 * w + Tile::drow(r, lane)][l16] = acc[r];
-    }
-    __syncthreads();
-    if (!first)
-        for (int e = tid; e < 64 * KBM; e += 256) {
-            const int i = e >> 4, j = e & 15;
-            sm.Y[i][j] -= (double)sm.Wp[0][i][j];
-        }
-    // B_c^T -= Z^T V^T over 16-row tiles: wave w takes tiles w, w + 4, ...
-    const int kbn = (n + 3) >> 2;
-    for (int64_t t0 = 16 * w; t0 < valid; t0 += 64) {
-        const int64_t row = t0 + l16;
-        T vv[16];
-#pragma unroll
-        for (int kb = 0; kb < 16; ++kb)
-            vv[kb] = (kb < kbn) ? v_elem<T>(Vc, ldv, row, 4 * kb + l4, valid, n, first) : T(0);
-        double b[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int col = Tile::drow(r, lane);
-            b[r] = 0.0;
-            if (row < valid && col < kc) {
-                if (first && !trans && row < n) b[r] = sm.Y[row][col];
-                else b[r] = Bin[row + (int64_t)col * ldbi];
-            }
-        }
-        Acc acc = Acc{0, 0, 0, 0};
-#pragma unroll
-        for (int kb = 0; kb < 16; ++kb) {
-            if (kb >= kbn) break;
-            acc = Tile::mfma(sm.Wp[0][4 * kb + l4][l16], vv[kb], acc);   // Z^T[col][refl] V^T
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int col = Tile::drow(r, lane);
-            if (row < valid && col < kc) {
-                const double out = b[r] - (double)acc[r];
-                if (first && trans && row < n) sm.Y[row][col] = out;
-                else Bout[row + (int64_t)col * ldbo] = out;
-            }
-        }
-    }
-    __syncthreads();
-}
-
-// Leaf part for domain `dom` and the 16-column block `cblk` of B.
-template <typename Tile>
-__device__ __forceinline__ void leaf_apply_domain(ApplyMSmem<Tile> &sm, const typename Tile::T *__restrict__ V,
-                                                  int64_t ldv, const double *__restrict__ Tc,
-                                                  const PanelArgs &pa, const double *__restrict__ Bsrc,
-                                                  int64_t ldbs, double *__restrict__ B, int64_t ldb, int64_t k,
-                                                  int trans, int64_t dom, int64_t cblk) {
-    const int64_t c0 = cblk * KBM;
-    const int kc = (int)((k - c0 < KBM) ? k - c0 : KBM);
+    using Smem = LeafApplySmem<Tile, NT, NB>;
+    constexpr int RT = Smem::RT, H = RT / 4;   // H rows per lane: lane, lane + 64
+    const int w = wave_index<4>();
+    int lane = threadIdx.x & 63;
     const int n = pa.n;
-    const int64_t row0 = dom_row0(pa, dom);
-    const int64_t nrows = dom_rows(pa, dom);
-    const int64_t nch = (nrows + pa.chunk - 1) / pa.chunk;
-    const int64_t nn = (int64_t)n * n;
-    const double *Bs0 = Bsrc + c0 * ldbs;
-    double *B0 = B + c0 * ldb;
-    const int tid = threadIdx.x;
-    if (trans) {
-        for (int64_t ch = 0; ch < nch; ++ch) {
-            const int64_t r0 = row0 + ch * pa.chunk;
-            const int64_t valid = (nrows - ch * pa.chunk < pa.chunk) ? nrows - ch * pa.chunk : pa.chunk;
-            chunk_apply_m<Tile>(sm, V + r0, ldv, Tc + (dom_chunk0(pa, dom) + ch) * nn, Bs0 + r0, ldbs, B0 + r0,
-                                ldb, valid, n, kc, ch == 0, 1);
+    const bool own = w < NT;   // this wave sums reflectors 16 w ..
+    T(*Vw)[16 * RT] = sm.V[w];
+    double(*Bw)[16 * RT] = reinterpret_cast<double(*)[16][16 * RT]>(sm.x)[w];
+    T(*Wx)[16 * NB] = reinterpret_cast<T(*)[16 * NB]>(sm.x);
+    Acc(*red)[64] = reinterpret_cast<Acc(*)[64]>(sm.x);
+    double(*Yx)[16 * NB] = reinterpret_cast<double(*)[16 * NB]>(sm.x);
+
+    // Rows past a short chunk repeat its last row (and are zero in B), columns
+    // past n column n - 1 (their rows of W are cleared, so that Z is zero
+    // there), columns past kc column kc - 1 (not stored).
+    T v[H][16 * NT];
+    double bl[H][16 * NB];
+    // part `i` of RT of the loads of chunk ch of an item
+    auto fetch = [&](const ApplyItem &it, int64_t ch, int i) {
+        const int64_t off = ch * pa.chunk;
+        const int valid = (int)(it.nrows - off < pa.chunk ? it.nrows - off : pa.chunk);
+        const T *Vc = Vp + it.row0 + off;
+        const double *Bc = Bsrcp + it.c0 * ldbs + it.row0 + off;
+        constexpr int CB = 16 * NB / 4, CV = 16 * NT / 4;
+        const int h = i >> 2, i4 = i & 3;
+        const int r = 16 * RT * w + 64 * h + lane, rc = r < valid ? r : valid - 1;
+#pragma unroll
+        for (int c = CB * i4; c < CB * (i4 + 1); ++c)
+            bl[h][c] = (Bc + (int64_t)(c < it.kc ? c : it.kc - 1) * ldbs)[rc];
+#pragma unroll
+        for (int c = CV * i4; c < CV * (i4 + 1); ++c) v[h][c] = (Vc + (int64_t)(c < n ? c : n - 1) * ldv)[rc];
+    };
+
+    ApplyItem it, nx;
+    int64_t g = blockIdx.x;
+    if (!apply_item<NB>(pa, k, ncb, g, it)) return;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) fetch(it, QT ? 0 : it.nch - 1, i);
+    const int64_t items = (pa.P + 7) / 8 * 8 * ncb;
+#pragma unroll 1
+    for (;;) {
+        // this item, and the next (a padding item has none after it)
+        g += gridDim.x;
+        const bool more = g < items && apply_item<NB>(pa, k, ncb, g, nx);
+        const int64_t row0 = it.row0, nrows = it.nrows, nch = it.nch;
+        const int kc = it.kc;
+        const double *Tk0 = Tc + dom_chunk0(pa, it.dom) * (int64_t)n * n;
+        const double *Bsrc = Bsrcp + it.c0 * ldbs + row0;
+        double *B = Bp + it.c0 * ldb + row0;
+        double y[NB][4];
+        int l16 = lane & 15, l4 = lane >> 4;
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * w + Tile::drow(r, lane), c = 16 * j + l16;
+                y[j][r] = 0.0;
+                if constexpr (!QT) {
+                    const double x = Bsrc[(row < n ? row : 0) + (int64_t)(c < kc ? c : kc - 1) * ldbs];
+                    y[j][r] = row < n ? x : 0.0;
+                }
+            }
+#pragma unroll 1
+        for (int64_t s = 0; s < nch; ++s) {
+            const int64_t ch = QT ? s : nch - 1 - s, off = ch * pa.chunk;
+            const int valid = (int)(nrows - off < pa.chunk ? nrows - off : pa.chunk);
+            const bool first = ch == 0;
+            // addresses are computed where they are used, not kept over the loop
+            asm volatile("" : "+v"(lane));
+            l16 = lane & 15;
+            l4 = lane >> 4;
+            if (first) {
+                if constexpr (!QT) {   // a first chunk's top rows are Yb
+                    __syncthreads();
+                    if (own) {
+#pragma unroll
+                        for (int j = 0; j < NB; ++j)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) Yx[16 * w + Tile::drow(r, lane)][16 * j + l16] = y[j][r];
+                    }
+                    __syncthreads();
+                    if (w == 0) {
+#pragma unroll
+                        for (int c = 0; c < 16 * NB; ++c) {
+                            const double x = Yx[lane < n ? lane : 0][c];
+                            bl[0][c] = lane < n ? x : bl[0][c];
+                        }
+                    }
+                    __syncthreads();
+                }
+                if (w == 0) {   // unit lower trapezoid
+#pragma unroll
+                    for (int c = 0; c < 16 * NT; ++c) v[0][c] = lane > c ? v[0][c] : (lane == c ? T(1) : T(0));
+                }
+            }
+            if (valid < (int)pa.chunk) {
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+#pragma unroll
+                    for (int c = 0; c < 16 * NB; ++c) bl[h][c] = 16 * RT * w + 64 * h + lane < valid ? bl[h][c] : 0.0;
+            }
+            double b[RT][NB][4];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) Bw[c][row_place<double>(64 * h + lane, c)] = bl[h][16 * j + c];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int h = 0; h < 4; h += 2) {
+                        const double2 p =
+                            *reinterpret_cast<const double2 *>(&Bw[l16][row_place<double>(16 * rt + 4 * l4 + h, l16)]);
+                        b[rt][j][h] = p.x;
+                        b[rt][j][h + 1] = p.y;
+                    }
+            }
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+                for (int c = 0; c < 16 * NT; ++c) Vw[c][row_place<T>(64 * h + lane, c)] = v[h][c];
+            // op(T)'s operand: entries (q, i) or (i, q), i = 16 w + l16, q = 16 t + 4 u + l4
+            const double *Tk = Tk0 + ch * (int64_t)n * n;
+            double tk[NT][4];
+            auto t_at = [&](int t, int u, bool &ok) {
+                const int i = 16 * w + l16, q = 16 * t + 4 * u + l4;
+                const int r = QT ? q : i, c = QT ? i : q;
+                ok = r <= c && c < n;
+                return ok ? r + c * n : 0;
+            };
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    bool ok;
+                    tk[t][u] = Tk[t_at(t, u, ok)];
+                }
+            asm volatile("" : "+v"(lane));
+            l16 = lane & 15;
+            l4 = lane >> 4;
+            // W over this wave's rows, the next chunk's loads spread over it
+            Acc acc[NT][NB];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[t][j] = Acc{0, 0, 0, 0};
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                if (s + 1 < nch) fetch(it, QT ? ch + 1 : ch - 1, rt);
+                else if (more) fetch(nx, QT ? 0 : nx.nch - 1, rt);
+                T a[NT][4];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    constexpr int kPer = 16 / sizeof(T);
+#pragma unroll
+                    for (int h = 0; h < 4; h += kPer) {
+                        typedef T Piece __attribute__((ext_vector_type(kPer)));
+                        const Piece p = *reinterpret_cast<const Piece *>(
+                            &Vw[16 * t + l16][row_place<T>(16 * rt + 4 * l4 + h, l16)]);
+#pragma unroll
+                        for (int i = 0; i < kPer; ++i) a[t][h + i] = p[i];
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        const T x = T(b[rt][j][r]);
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) acc[t][j] = Tile::mfma(a[t][r], x, acc[t][j]);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // the partials meet: W's rows 16 w .. on wave w
+            Acc wv[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                __syncthreads();
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    if (t == w) wv[j] = acc[t][j];
+                    else red[3 * t + (w < t ? w : w - 1)][lane] = acc[t][j];
+                }
+                __syncthreads();
+                if (own) {
+                    wv[j] = wv[j] + red[3 * w][lane] + red[3 * w + 1][lane] + red[3 * w + 2][lane];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (!first) wv[j][r] += T(y[j][r]);
+                        wv[j][r] = 16 * w + Tile::drow(r, lane) < n ? wv[j][r] : T(0);
+                    }
+                }
+            }
+            __syncthreads();
+            if (own) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) Wx[16 * w + Tile::drow(r, lane)][16 * j + l16] = wv[j][r];
+            }
+            __syncthreads();
+            Acc z[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) z[j] = Acc{0, 0, 0, 0};
+            if (own) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    if (QT ? t <= w : t >= w) {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            bool ok;
+                            t_at(t, u, ok);
+                            const T a = ok ? T(tk[t][u]) : T(0);
+#pragma unroll
+                            for (int j = 0; j < NB; ++j)
+                                z[j] = Tile::mfma(a, Wx[16 * t + 4 * u + l4][16 * j + l16], z[j]);
+                        }
+                    }
+            }
+            __syncthreads();
+            if (own) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (!first) y[j][r] -= (double)z[j][r];
+                        Wx[16 * w + Tile::drow(r, lane)][16 * j + l16] = -z[j][r];
+                    }
+            }
+            __syncthreads();
+            T zb[NT][4][NB];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) zb[t][u][j] = Wx[16 * t + 4 * u + l4][16 * j + l16];
+            __syncthreads();
+            asm volatile("" : "+v"(lane));
+            l16 = lane & 15;
+            l4 = lane >> 4;
+            // B - V Z
+            const int prow = tile_row_of<Tile>(l16);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                Acc c[NB];
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    if constexpr (sizeof(T) == 8) c[j] = Acc{b[rt][j][0], b[rt][j][1], b[rt][j][2], b[rt][j][3]};
+                    else c[j] = Acc{0, 0, 0, 0};
+                }
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int col = 16 * t + 4 * u + l4;
+                        const T a = Vw[col][row_place<T>(16 * rt + prow, 4 * u + l4)];
+#pragma unroll
+                        for (int j = 0; j < NB; ++j) c[j] = Tile::mfma(a, zb[t][u][j], c[j]);
+                    }
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if constexpr (sizeof(T) == 8) b[rt][j][r] = c[j][r];
+                        else b[rt][j][r] += (double)c[j][r];
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (first && QT) {   // Yb starts as a first chunk's top rows
+                if (w == 0) {
+#pragma unroll
+                    for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+                        for (int j = 0; j < NB; ++j)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) Yx[16 * rt + 4 * l4 + r][16 * j + l16] = b[rt][j][r];
+                }
+                __syncthreads();
+                if (own) {
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) y[j][r] = Yx[16 * w + Tile::drow(r, lane)][16 * j + l16];
+                }
+                __syncthreads();
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" : "+v"(lane));
+            l16 = lane & 15;
+            l4 = lane >> 4;
+            const int lo = (first && QT && w == 0) ? n : 0;   // rows that became Yb
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int h = 0; h < 4; h += 2)
+                        *reinterpret_cast<double2 *>(&Bw[l16][row_place<double>(16 * rt + 4 * l4 + h, l16)]) =
+                            double2{b[rt][j][h], b[rt][j][h + 1]};
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    const int r = 64 * h + lane;
+                    double o[16];
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) o[c] = Bw[c][row_place<double>(r, c)];
+                    if (16 * RT * w + r < valid && r >= lo) {
+#pragma unroll
+                        for (int c = 0; c < 16; ++c)
+                            if (16 * j + c < kc) (B + off + (int64_t)(16 * j + c) * ldb)[16 * RT * w + r] = o[c];
+                    }
+                }
+            }
         }
-        for (int e = tid; e < 64 * KBM; e += 256) {
-            const int r = e >> 4, c = e & 15;
-            if (r < n && c < kc) B0[row0 + r + (int64_t)c * ldb] = sm.Y[r][c];
+        if constexpr (QT) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * w + Tile::drow(r, lane), c = 16 * j + l16;
+                    if (c < kc && row < n) B[row + (int64_t)c * ldb] = y[j][r];
+                }
         }
-    } else {
-        for (int e = tid; e < 64 * KBM; e += 256) {
-            const int r = e >> 4, c = e & 15;
-            sm.Y[r][c] = (r < n && c < kc) ? Bs0[row0 + r + (int64_t)c * ldbs] : 0.0;
-        }
-        __syncthreads();
-        for (int64_t ch = nch - 1; ch >= 0; --ch) {
-            const int64_t r0 = row0 + ch * pa.chunk;
-            const int64_t valid = (nrows - ch * pa.chunk < pa.chunk) ? nrows - ch * pa.chunk : pa.chunk;
-            chunk_apply_m<Tile>(sm, V + r0, ldv, Tc + (dom_chunk0(pa, dom) + ch) * nn, Bs0 + r0, ldbs, B0 + r0,
-                                ldb, valid, n, kc, ch == 0, 0);
-        }
+        if (!more) return;
+        it = nx;
     }
 }
 
-// Workgroup order: groups of 8 domains x ncb column blocks, the column
-// blocks of one domain 8 workgroups apart.  Workgroups go to the 8 XCDs
-// round-robin by index, so a domain's column blocks share one XCD (one L2)
-// and run side by side: its V comes from HBM about once instead of ncb times.
-template <typename Tile>
-__global__ __launch_bounds__(256) void k_leaf_apply_m(const typename Tile::T *__restrict__ V, int64_t ldv,
-                                                      const double *__restrict__ Tc, PanelArgs pa,
-                                                      const double *__restrict__ Bsrc, int64_t ldbs,
-                                                      double *__restrict__ B, int64_t ldb, int64_t k,
-                                                      int trans, int ncb) {
-    extern __shared__ double smem_raw[];
-    ApplyMSmem<Tile> &sm = *reinterpret_cast<ApplyMSmem<Tile> *>(smem_raw);
-    const int64_t b = blockIdx.x, per = 8 * (int64_t)ncb;
-    const int64_t within = b % per;
-    const int64_t dom = (b / per) * 8 + within % 8;
-    const int64_t cblk = within / 8;
-    if (dom >= pa.P) return;
-    leaf_apply_domain<Tile>(sm, V, ldv, Tc, pa, Bsrc, ldbs, B, ldb, k, trans, dom, cblk);
+template <typename Tile, int NT, int NB, bool QT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
+void k_leaf_apply_m(const typename Tile::T *__restrict__ V, int64_t ldv, const double *__restrict__ Tc,
+                    PanelArgs pa, const double *Bsrc, int64_t ldbs, double *B, int64_t ldb, int64_t k, int ncb) {
+    extern __shared__ __attribute__((aligned(64))) unsigned char smem_bytes[];
+    auto &sm = *reinterpret_cast<LeafApplySmem<Tile, NT, NB> *>(smem_bytes);
+    leaf_apply_chains<Tile, NT, NB, QT>(sm, V, ldv, Tc, pa, Bsrc, ldbs, B, ldb, k, ncb);
 }
 
-template <typename Tile>
-static hipError_t launch_apply_m(const typename Tile::T *V, int64_t ldv, const double *Tc,
-                                 const PanelArgs &pa, const double *Bsrc, int64_t ldbs, double *B,
-                                 int64_t ldb, int64_t k, int trans, const char *tag, hipStream_t st) {
-    if (k <= 0) return hipSuccess;
-    const size_t sh = sizeof(ApplyMSmem<Tile>);
-    hipError_t e = hipFuncSetAttribute((const void *)k_leaf_apply_m<Tile>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+// As many workgroups as the compute units hold (by LDS).
+template <typename Tile, int NT, int NB, bool QT>
+static hipError_t launch_apply_m(const typename Tile::T *V, int64_t ldv, const double *Tc, const PanelArgs &pa,
+                                 const double *Bsrc, int64_t ldbs, double *B, int64_t ldb, int64_t k,
+                                 const char *tag, hipStream_t st) {
+    const size_t sh = sizeof(LeafApplySmem<Tile, NT, NB>);
+    const auto kern = k_leaf_apply_m<Tile, NT, NB, QT>;
+    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
-    const int ncb = (int)((k + KBM - 1) / KBM);
-    const int64_t groups = (pa.P + 7) / 8;
+    const int ncb = (int)((k + 16 * NB - 1) / (16 * NB));
+    const int64_t items = (pa.P + 7) / 8 * 8 * ncb, cap = kComputeUnits * (int64_t)(160 * 1024 / sh);
     ProfScope ps(tag, st);
-    hipLaunchKernelGGL(k_leaf_apply_m<Tile>, dim3((unsigned)(groups * 8 * ncb)), dim3(256), sh, st, V, ldv, Tc,
-                       pa, Bsrc, ldbs, B, ldb, k, trans, ncb);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(items < cap ? items : cap)), dim3(256), sh, st, V, ldv, Tc, pa, Bsrc,
+                       ldbs, B, ldb, k, ncb);
     return hipGetLastError();
+}
+
+// 32 columns per workgroup read V half as often and share each of its LDS
+// reads between two tiles, but only where that still gives every compute
+// unit a workgroup: a chunk then takes 30 thousand cycles against 2 x 21.
+template <typename Tile>
+static hipError_t launch_apply_m(const typename Tile::T *V, int64_t ldv, const double *Tc, const PanelArgs &pa,
+                                 const double *Bsrc, int64_t ldbs, double *B, int64_t ldb, int64_t k, int trans,
+                                 const char *tag, hipStream_t st) {
+    if (k <= 0) return hipSuccess;
+    const bool wide = k > 16 && pa.P * ((k + 31) / 32) >= kComputeUnits;
+    auto go = [&](auto nt, auto nb, auto qt) {
+        return launch_apply_m<Tile, decltype(nt)::value, decltype(nb)::value, decltype(qt)::value>(
+            V, ldv, Tc, pa, Bsrc, ldbs, B, ldb, k, tag, st);
+    };
+    auto with_nt = [&](auto nb, auto qt) {
+        switch ((pa.n + 15) >> 4) {
+            case 1: return go(std::integral_constant<int, 1>{}, nb, qt);
+            case 2: return go(std::integral_constant<int, 2>{}, nb, qt);
+            case 3: return go(std::integral_constant<int, 3>{}, nb, qt);
+            default: return go(std::integral_constant<int, 4>{}, nb, qt);
+        }
+    };
+    auto with_nb = [&](auto qt) {
+        return wide ? with_nt(std::integral_constant<int, 2>{}, qt) : with_nt(std::integral_constant<int, 1>{}, qt);
+    };
+    return trans ? with_nb(std::true_type{}) : with_nb(std::false_type{});
 }
 
 hipError_t launch_leaf_apply_m(const double *V, int64_t ldv, const double *Tc, const PanelArgs &pa,

@@ -6,6 +6,8 @@
 
 namespace tsqr {
 
+constexpr int64_t kComputeUnits = 256;  // compute units of one gfx950 GPU (MI355X)
+
 // Row stride (in doubles) of the n x n triangles staged in LDS; odd so that
 // reads down a column of the row-major copy hit distinct banks.
 constexpr int kLdsStride = 65;

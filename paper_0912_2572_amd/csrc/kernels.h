@@ -147,8 +147,7 @@ hipError_t launch_sign_normalise(const double *Rroot, int n, double *Rout, int64
 
 // apply.hip: Q^T (trans = 1) or Q (trans = 0) of a panel's leaves / tree on
 // k columns.  Bsrc may differ from B (out of place) or equal it.
-// apply_mfma.hip: the same leaf application on FP64 matrix cores
-// (16 columns of B per workgroup).
+// apply_mfma.hip: the leaf application (16 or 32 columns of B per workgroup).
 hipError_t launch_leaf_apply_m(const double *V, int64_t ldv, const double *Tc, const PanelArgs &pa,
                                const double *Bsrc, int64_t ldbs, double *B, int64_t ldb, int64_t k,
                                int trans, hipStream_t st);
