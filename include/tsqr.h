@@ -372,8 +372,8 @@ TSQR_API int tsqr_calu(int64_t m, int64_t n, double *A, int64_t lda, const tsqr_
    the Cholesky work the conclusion cites: block columns of 256 columns,
    whose trailing update A22 -= L21 L21^T runs on the FP64 matrix cores (the
    trailing matrix is read and written once per block column), each factored
-   in 64-column panels (the 64 x 64 diagonal block in one wave, the rows
-   below solved against it, 64 rows per workgroup).
+   in 64-column panels (the 64 x 64 diagonal block by the workgroup that
+   updated it, the rows below solved against it, 16 rows per wave).
    A (n x n, device, column-major, lda >= max(1, n)): in, the lower triangle
    of the SPD matrix (the strict upper triangle is neither read nor
    written); out, L in the lower triangle.

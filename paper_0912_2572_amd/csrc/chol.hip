@@ -5,14 +5,13 @@
 // Blocked right-looking Cholesky.  Block columns of kOuter = 256 columns;
 // inside one, panels of kPanel = 64 columns:
 //
-//   k_chol_panel   per panel: the 64 x 64 diagonal block factored in one
-//                  wave (lane t holds row t; column k of L goes through LDS
-//                  and comes back to every lane as broadcasts), then every
-//                  row below the block solved against it, l_i = a_i
-//                  L11^{-T} (one wave per 32 rows, a lane pair per row
-//                  splitting its columns by parity).  Every workgroup
-//                  factors the diagonal block itself, so one launch covers
-//                  the panel;
+//   chol_diagonal  a 64 x 64 diagonal block in 16-column panels: a panel's
+//                  steps on one wave (lane = row, the panel's entries in
+//                  registers), its update of the later columns as matrix-core
+//                  tiles by four waves.  The first block has a launch of its
+//                  own; every later one is tile (0, 0) of the update before it,
+//                  whose workgroup factors it while the other tiles run;
+//   k_chol_solve   the rows below it, l_i = a_i L11^{-T}, 16 rows a wave;
 //   k_chol_update  C -= W W^T on the lower triangle of a trailing block:
 //                  with W the panel inside its block column (K = 64, the
 //                  columns of the rest of the block column), then with W
@@ -33,6 +32,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "mfma.h"
+#include "panel_qr.h"
 #include "prof.h"
 
 namespace tsqr {
@@ -52,156 +52,201 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
     return r;
 }
 
-// The steps of the panel kernel, unrolled by template recursion so that
-// every register index is a compile-time constant.  A step reads its
-// column of L11 from LDS into registers and marks each value as used, in
-// order, with an empty asm statement: every load is then issued before the
-// first use instead of one load in front of each use.
+constexpr int kDiagLd = 65;   // row stride of a diagonal block in LDS
 
-// Column K of L11 in LDS: L(i, K), i != K, at lc_at(K, i) (the even rows,
-// then the odd ones, so that a lane pair's halves are contiguous); 1 /
-// L(K, K) at 64 * 64 + K.
-__host__ __device__ constexpr int lc_at(int K, int i) { return kPanel * K + 32 * (i & 1) + (i >> 1); }
-
-// Factorization step K: lane t holds row t of the diagonal block in m.
+// Step K of panel p of a diagonal block on one wave: lane = row, its entries
+// of columns 16 p .. 16 p + 15 in m; the panel's own rows 16 p + lane % 16 once
+// more in dg, on every 16-lane row, so that their entries of column K of L are
+// DPP operands of the updates.  Column K is left in m[K].  Entries above the
+// diagonal hold values that nothing reads.  fail: the first column whose pivot
+// is not positive (the steps after it go on with what is there).
 template <int K>
-struct FactorStep {
-    __device__ __forceinline__ static void run(double (&m)[kPanel], double *Lc, int t, int sb, int &fail) {
-        if (K < sb && fail < 0) {
-            const double d = wave_bcast(m[K], K);
-            if (!(d > 0.0)) {
-                fail = K;
-            } else {
-                const double rinv = rsqrt_f64(d);
-                const double v = t < K ? 0.0 : (t == K ? d * rinv : m[K] * rinv);
-                m[K] = v;
-                if (t == K) Lc[kPanel * kPanel + K] = rinv;
-                else Lc[lc_at(K, t)] = v;
-                __syncthreads();
-                constexpr int R = kPanel - K - 1;
-                if constexpr (R > 0) {
-                    double cv[R];
+struct DiagStep {
+    __device__ __forceinline__ static void run(double (&m)[16], double (&dg)[16], int p, int &fail) {
+        const double d = row_bcast<K>(dg[K]);
+        fail = (fail < 0 && !(d > 0.0)) ? 16 * p + K : fail;
+        const double rinv = rsqrt_f64(d);
+        const double v = m[K] * rinv, vd = dg[K] * rinv;
+        m[K] = v;
+        row_terms<K + 1>(dg, -vd, vd);
+        row_terms<K + 1>(m, -vd, v);
+        if constexpr (K + 1 < 16) DiagStep<K + 1>::run(m, dg, p, fail);
+    }
+};
+
+// Cholesky factor of the 64 x 64 block in S (its lower triangle; rows past
+// the block's order hold the identity) by four waves, in place.  Returns the
+// first column whose pivot is not positive, or -1, on wave 0.  What bounds
+// it: the chain of 64 steps (pivot broadcast, reciprocal square root, the
+// panel's update), about 200 cycles each; 300 with the column's entries read
+// lane by lane into scalars.
+__device__ __forceinline__ int chol_diagonal(double *S) {
+    const int w = wave_index<4>(), lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+    int fail = -1;
+#pragma unroll 1
+    for (int p = 0; p < 4; ++p) {
+        if (w == 0) {
+            double m[16], dg[16];
+            double *row = S + lane * kDiagLd + 16 * p, *own = S + (16 * p + l16) * kDiagLd + 16 * p;
 #pragma unroll
-                    for (int i = 0; i < R; ++i) cv[i] = Lc[lc_at(K, K + 1 + i)];
-#pragma unroll
-                    for (int i = 0; i < R; ++i) asm volatile("" : "+v"(cv[i]));
-#pragma unroll
-                    for (int i = 0; i < R; ++i) m[K + 1 + i] = fma(-v, cv[i], m[K + 1 + i]);
-                }
+            for (int j = 0; j < 16; ++j) {
+                m[j] = row[j];
+                dg[j] = own[j];
             }
+            DiagStep<0>::run(m, dg, p, fail);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) row[j] = m[j];
         }
-        FactorStep<K + 1>::run(m, Lc, t, sb, fail);
+        __syncthreads();
+        // tiles (a, s), p < s <= a, dealt to the waves
+        int e = 0;
+        for (int s = p + 1; s < 4; ++s)
+            for (int a = s; a < 4; ++a, ++e) {
+                if ((e & 3) != w) continue;
+                d4 c;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) c[r] = S[(16 * a + 4 * r + l4) * kDiagLd + 16 * s + l16];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    c = mfma_f64(-S[(16 * a + l16) * kDiagLd + 16 * p + 4 * u + l4],
+                                 S[(16 * s + l16) * kDiagLd + 16 * p + 4 * u + l4], c);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) S[(16 * a + 4 * r + l4) * kDiagLd + 16 * s + l16] = c[r];
+            }
+        __syncthreads();
     }
-};
-template <>
-struct FactorStep<kPanel> {
-    __device__ __forceinline__ static void run(double (&)[kPanel], double *, int, int, int &) {}
-};
+    return fail;
+}
 
-// Solve step K on a lane pair: lane h = lane & 1 of the pair holds the
-// columns j = 2 q + h of its row in xh[q].  The owner of column K (h = K & 1)
-// forms x_K = x_K / L(K, K) and passes it to its partner by DPP; each lane
-// then updates its columns past K with column K of L11, its half read from
-// LDS in one batch.
-template <int K>
-struct PairSolveStep {
-    __device__ __forceinline__ static void run(double (&xh)[kPanel / 2], const double *Lc, int h, int sb) {
-        if (K < sb) {
-            constexpr int hK = K & 1, qK = K >> 1, Q0 = K >> 1, R = kPanel / 2 - Q0;
-            const double own = xh[qK] * Lc[kPanel * kPanel + K];
-            // the exchange runs on the whole wave before the select (inside
-            // a branch on the non-owners it would read lanes that are off)
-            double other = dpp_f64<kDppXor1>(own);
-            asm volatile("" : "+v"(other));
-            const double xk = (h == hK) ? own : other;
-            if (h == hK) xh[qK] = xk;
-            double cv[R];
-            const double *col = Lc + kPanel * K + 32 * h;
-#pragma unroll
-            for (int q = 0; q < R; ++q) cv[q] = col[Q0 + q];
-#pragma unroll
-            for (int q = 0; q < R; ++q) asm volatile("" : "+v"(cv[q]));
-#pragma unroll
-            for (int q = 0; q < R; ++q)
-                if (2 * (Q0 + q) + h > K) xh[Q0 + q] = fma(-xk, cv[q], xh[Q0 + q]);
-        }
-        PairSolveStep<K + 1>::run(xh, Lc, h, sb);
+// The factored block's lower triangle to A, or the failed column to dinfo.
+__device__ __forceinline__ void chol_diagonal_out(const double *S, double *__restrict__ A, int64_t lda, int64_t s,
+                                                  int sb, int fail, int *flag, int32_t *__restrict__ dinfo) {
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (t == 0) *flag = fail;
+    __syncthreads();
+    if (*flag >= 0) {
+        if (t == 0) *dinfo = (int32_t)(s + *flag + 1);
+        return;
     }
-};
-template <>
-struct PairSolveStep<kPanel> {
-    __device__ __forceinline__ static void run(double (&)[kPanel / 2], const double *, int, int) {}
-};
+    double *Ad = A + s + s * lda;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int c = w + 4 * u;
+        if (c <= lane && lane < sb) Ad[lane + c * lda] = S[lane * kDiagLd + c];
+    }
+}
 
 __global__ __launch_bounds__(64) void k_chol_info_clear(int32_t *dinfo) {
     if (threadIdx.x == 0) *dinfo = 0;
 }
 
-// Panel of columns s .. s + sb - 1 (1 <= sb <= 64): the diagonal block
-// (rows s .. s + sb - 1) and the rows s + sb + 32 blockIdx.x + lane / 2.
-// Both phases read a column of L11 from LDS as broadcasts, all of its
-// loads issued before the first use.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void k_chol_panel(double *__restrict__ A, int64_t lda, int64_t n, int64_t s, int sb,
-                  int32_t *__restrict__ dinfo) {
-    if (*(volatile int32_t *)dinfo != 0) return;
-    // column k of L11 at lc_at(k, i) (rows >= sb zero), 1 / L(k, k) at
-    // 64 * 64 + k
-    __shared__ double Lc[kPanel * kPanel + kPanel];
-    const int t = threadIdx.x;
-    double *__restrict__ Ad = A + s + s * lda;
-
-    // Row t of the diagonal block, lower part (rows past sb stay zero).
-    double m[kPanel];
+__global__ __launch_bounds__(256) void k_chol_diag(double *__restrict__ A, int64_t lda, int sb,
+                                                   int32_t *__restrict__ dinfo) {
+    __shared__ double S[kPanel * kDiagLd];
+    __shared__ int flag;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
 #pragma unroll
-    for (int j = 0; j < kPanel; ++j) m[j] = (j < sb && j <= t && t < sb) ? Ad[t + j * lda] : 0.0;
-
-    // Right-looking factorization: step k finishes column k of L and updates
-    // the columns after it.
-    int fail = -1;
-    FactorStep<0>::run(m, Lc, t, sb, fail);
-    if (fail >= 0) {
-        if (t == 0) *dinfo = (int32_t)(s + fail + 1);
-        return;
-    }
-    if (blockIdx.x == 0 && t < sb) {
-#pragma unroll
-        for (int j = 0; j < kPanel; ++j)
-            if (j <= t) Ad[t + j * lda] = m[j];
+    for (int u = 0; u < 16; ++u) {
+        const int c = w + 4 * u;
+        const double v = A[(c <= lane && lane < sb) ? lane + c * lda : 0];
+        S[lane * kDiagLd + c] = lane < sb ? (c <= lane ? v : 0.0) : (c == lane ? 1.0 : 0.0);
     }
     __syncthreads();
-
-    // Rows below: x L11^T = a by forward substitution, a lane pair per row
-    // (32 rows per workgroup), lane h of the pair on the columns 2 q + h.
-    const int h = t & 1;
-    const int64_t r = s + sb + (int64_t)blockIdx.x * (kPanel / 2) + (t >> 1);
-    const bool rok = r < n;
-    double *__restrict__ Ar = A + (rok ? r : 0) + s * lda;
-    double xh[kPanel / 2];
-#pragma unroll
-    for (int q = 0; q < kPanel / 2; ++q) xh[q] = (rok && 2 * q + h < sb) ? Ar[(2 * q + h) * lda] : 0.0;
-    PairSolveStep<0>::run(xh, Lc, h, sb);
-    if (!rok) return;
-#pragma unroll
-    for (int q = 0; q < kPanel / 2; ++q)
-        if (2 * q + h < sb) Ar[(2 * q + h) * lda] = xh[q];
+    const int fail = chol_diagonal(S);
+    chol_diagonal_out(S, A, lda, 0, sb, fail, &flag, dinfo);
 }
 
-// C(i, c) -= sum_{k < K} A(i, kc + k) A(c, kc + k) for t0 <= c < cend,
-// c <= i < n: the lower triangle of a trailing block, by TILE x TILE tiles
-// (bi, bc), bc <= bi, numbered column after column.  Four waves in a 2 x 2
-// grid of (TILE/2) x (TILE/2) sub-tiles.
-template <int TILE>
-__global__ __launch_bounds__(256) void k_chol_update(double *__restrict__ A, int64_t lda, int64_t n, int64_t t0,
-                                                     int64_t cend, int64_t kc, int K, int64_t Tr, int64_t Tc,
-                                                     const int32_t *__restrict__ dinfo) {
+// x L11^T = a on 16 columns: u[K] = u[K] / L(K, K), then u[j] -= u[K] L(j, K),
+// row j of -L11 in lane j of every 16-lane row (column K: nl[K]), 1 / L(j, j)
+// in lane j (ri).
+template <int K>
+struct LowerSolve {
+    __device__ __forceinline__ static void run(double (&u)[16], const double (&nl)[16], double ri) {
+        u[K] *= wave_bcast(ri, K);
+        if constexpr (K < 15) {
+            row_terms<K + 1>(u, nl[K], u[K]);
+            LowerSolve<K + 1>::run(u, nl, ri);
+        }
+    }
+};
+
+// Rows s + 64 + 16 blockIdx.x + 0 .. 15 of panel s .. s + 63 against its
+// factored diagonal block, on one wave, right-looking over four 16-column
+// tiles.  A tile waits as a transposed matrix-core accumulator (lane: row
+// lane % 16, columns 4 r + lane / 16); when its turn comes it passes through
+// LDS so that every 16-lane row holds whole rows of it (lane = row, 16 columns
+// in registers), is solved with the entries of its diagonal tile as DPP
+// operands, and updates the tiles after it.  What bounds it: latency -- the
+// loads, then 4 x 136 multiply-adds and 24 matrix-core tiles in a chain (about
+// 5 thousand cycles); 16 rows a wave give 8,192 rows two waves per unit.
+// Measured: 9.4 us a panel of 8,192 rows; 16.4 us with 64 rows a wave, all
+// 2,016 multiply-adds on one lane, and 46 us for the diagonal block in every
+// workgroup and the solve in one kernel.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2)))
+void k_chol_solve(double *__restrict__ A, int64_t lda, int64_t n, int64_t s, const int32_t *__restrict__ dinfo) {
+    __shared__ double X[16][17];   // [column][row]
     if (*(const volatile int32_t *)dinfo != 0) return;
-    constexpr int WT = TILE / 32;       // 16 x 16 tiles per wave and dimension
-    constexpr int KSTEP = 256 / TILE;   // loader: k stride between one thread's loads
-    constexpr int LPT = TILE / 16;      // loads per thread and operand per chunk
-    static_assert(KSTEP * LPT == 16, "16-column chunks");
-    __shared__ double As[2][16][TILE];
-    __shared__ double Bs[2][16][TILE];
+    const int lane = threadIdx.x, l16 = lane & 15, l4 = lane >> 4;
+    const double *__restrict__ Ld = A + s + s * lda;
+    const int64_t r = s + kPanel + (int64_t)blockIdx.x * 16 + l16;
+    double *__restrict__ Ar = A + (r < n ? r : n - 1) + s * lda;
+    d4 c[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c[t][q] = Ar[(16 * t + 4 * q + l4) * lda];
+    double nl[4][16], dg[4], lo[4][4][4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        dg[p] = Ld[(16 * p + l16) * (lda + 1)];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) nl[p][k] = Ld[16 * p + l16 + (16 * p + (k < l16 ? k : l16)) * lda];
+#pragma unroll
+        for (int t = p + 1; t < 4; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) lo[p][t][q] = Ld[16 * t + l16 + (16 * p + 4 * q + l4) * lda];
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) X[4 * q + l4][l16] = c[p][q];
+        __syncthreads();
+        double u[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) u[k] = X[k][l16];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) nl[p][k] = k < l16 ? -nl[p][k] : 0.0;
+        LowerSolve<0>::run(u, nl[p], 1.0 / dg[p]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double x = l4 & 2 ? (l4 & 1 ? u[4 * q + 3] : u[4 * q + 2]) : (l4 & 1 ? u[4 * q + 1] : u[4 * q]);
+            if (r < n) Ar[(16 * p + 4 * q + l4) * lda] = x;
+#pragma unroll
+            for (int t = p + 1; t < 4; ++t) c[t] = mfma_f64(-lo[p][t][q], x, c[t]);
+        }
+    }
+}
+
+// C(i, c) -= sum_{k < 16 nch} A(i, kc + k) A(c, kc + k) for t0 <= c < cend,
+// c <= i < n: the lower triangle of a trailing block, by 64 x 64 tiles
+// (bi, bc), bc <= bi, numbered column after column.  Four waves in a 2 x 2
+// grid of 32 x 32 sub-tiles.  Tile (0, 0) is the next panel's diagonal block:
+// its workgroup goes on to factor it.
+// A 16-column chunk of both operands sits in LDS, two columns side by side (a
+// 16-byte read feeds two products), the next chunk's loads in flight; rows
+// past the end repeat the last row and nothing in the loop is conditional, so
+// that the accumulators stay where the matrix cores write them.  The product is formed transposed: a store covers 16
+// rows of a column.
+__global__ __launch_bounds__(256, 4) void k_chol_update(double *__restrict__ A, int64_t lda, int64_t n, int64_t t0,
+                                                     int64_t cend, int64_t kc, int nch, int64_t Tr, int64_t Tc,
+                                                     int32_t *__restrict__ dinfo) {
+    if (*(const volatile int32_t *)dinfo != 0) return;
+    __shared__ __attribute__((aligned(16))) double smem[kPanel * kDiagLd];   // operands, then the diagonal block
+    __shared__ int flag;
+    double2(*As)[8][kPanel] = reinterpret_cast<double2(*)[8][kPanel]>(smem);   // [buffer][columns 2 q, 2 q + 1][row]
+    double2(*Bs)[8][kPanel] = As + 2;
+    static_assert(4 * 16 * kPanel <= kPanel * kDiagLd, "both operands, double-buffered");
 
     // tile id -> (bi, bc): column bc starts at bc Tr - bc (bc - 1) / 2
     const int64_t id = blockIdx.x;
@@ -213,91 +258,120 @@ __global__ __launch_bounds__(256) void k_chol_update(double *__restrict__ A, int
     }
     const int64_t bc = lo;
     const int64_t bi = bc + (id - (bc * Tr - bc * (bc - 1) / 2));
-    const int64_t i0 = t0 + bi * TILE, c0 = t0 + bc * TILE;
+    const int64_t i0 = t0 + bi * kPanel, c0 = t0 + bc * kPanel;
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int w = wave_index<4>(), lane = threadIdx.x & 63;
     const int wi = w >> 1, wj = w & 1;
-    // on a diagonal tile the upper-right sub-tile is above the diagonal
-    const bool idle = (bi == bc) && (wi < wj);
 
-    const int lrow = tid % TILE, lk = tid / TILE;
-    const int64_t ar = i0 + lrow, br = c0 + lrow;
-    const bool aok = ar < n, bok = br < n;
-    const double *__restrict__ Aa = A + (aok ? ar : 0) + kc * lda;
-    const double *__restrict__ Ab = A + (bok ? br : 0) + kc * lda;
-
-    d4 acc[WT][WT];
+    // wave w loads columns 4 w .. 4 w + 3 of a chunk, lane = row
+    const double *Aa = A + (i0 + lane < n ? i0 + lane : n - 1) + (kc + 4 * w) * lda;
+    const double *Ab = A + (c0 + lane < n ? c0 + lane : n - 1) + (kc + 4 * w) * lda;
+    double ra[4], rb[4];
+    auto load = [&] {
 #pragma unroll
-    for (int I = 0; I < WT; ++I)
-#pragma unroll
-        for (int J = 0; J < WT; ++J) acc[I][J] = d4_zero();
-
-    double ra[LPT], rb[LPT];
-    auto load = [&](int ch) {
-#pragma unroll
-        for (int q = 0; q < LPT; ++q) {
-            const int k = 16 * ch + lk + KSTEP * q;
-            ra[q] = (aok && k < K) ? Aa[k * lda] : 0.0;
-            rb[q] = (bok && k < K) ? Ab[k * lda] : 0.0;
+        for (int q = 0; q < 4; ++q) {
+            ra[q] = Aa[q * lda];
+            rb[q] = Ab[q * lda];
         }
+        Aa += 16 * lda;
+        Ab += 16 * lda;
     };
     auto stash = [&](int buf) {
 #pragma unroll
-        for (int q = 0; q < LPT; ++q) {
-            As[buf][lk + KSTEP * q][lrow] = ra[q];
-            Bs[buf][lk + KSTEP * q][lrow] = rb[q];
+        for (int q = 0; q < 4; q += 2) {
+            As[buf][2 * w + q / 2][lane] = double2{ra[q], ra[q + 1]};
+            Bs[buf][2 * w + q / 2][lane] = double2{rb[q], rb[q + 1]};
         }
     };
 
-    const int nch = (K + 15) / 16;
-    load(0);
+    load();
+    // this lane's entries of C: row crow of sub-tile I, columns ccol + 4 r of J
+    d4 acc[2][2];
+    auto crow = [&](int I) { return i0 + 32 * wi + 16 * I + d_col(lane); };
+    auto ccol = [&](int J, int r) { return c0 + 32 * wj + 16 * J + d_row(r, lane); };
+#pragma unroll
+    for (int I = 0; I < 2; ++I)
+#pragma unroll
+        for (int J = 0; J < 2; ++J) acc[I][J] = d4_zero();
     stash(0);
     __syncthreads();
-    const int ri = wi * (TILE / 2) + (lane & 15), rj = wj * (TILE / 2) + (lane & 15);
+    const int ri = 32 * wi + (lane & 15), rj = 32 * wj + (lane & 15), kq = lane >> 4;
+#pragma unroll 1
     for (int ch = 0; ch < nch; ++ch) {
         const int buf = ch & 1;
-        if (ch + 1 < nch) load(ch + 1);
-        if (!idle) {
+        if (ch + 1 < nch) load();
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int kk = 4 * ks + (lane >> 4);
-                double a[WT], b[WT];
+        for (int ks = 0; ks < 2; ++ks) {
+            double2 a[2], b[2];
 #pragma unroll
-                for (int I = 0; I < WT; ++I) a[I] = As[buf][kk][ri + 16 * I];
+            for (int I = 0; I < 2; ++I) a[I] = As[buf][4 * ks + kq][ri + 16 * I];
 #pragma unroll
-                for (int J = 0; J < WT; ++J) b[J] = Bs[buf][kk][rj + 16 * J];
+            for (int J = 0; J < 2; ++J) b[J] = Bs[buf][4 * ks + kq][rj + 16 * J];
 #pragma unroll
-                for (int I = 0; I < WT; ++I)
+            for (int I = 0; I < 2; ++I)
 #pragma unroll
-                    for (int J = 0; J < WT; ++J) acc[I][J] = mfma_f64(a[I], b[J], acc[I][J]);
-            }
+                for (int J = 0; J < 2; ++J) acc[I][J] = mfma_f64(b[J].x, a[I].x, acc[I][J]);
+#pragma unroll
+            for (int I = 0; I < 2; ++I)
+#pragma unroll
+                for (int J = 0; J < 2; ++J) acc[I][J] = mfma_f64(b[J].y, a[I].y, acc[I][J]);
         }
         if (ch + 1 < nch) stash(buf ^ 1);
         __syncthreads();
     }
-    if (idle) return;
-
+    // C in one batch of loads, the sum subtracted from it
+    d4 cc[2][2];
 #pragma unroll
-    for (int I = 0; I < WT; ++I)
+    for (int I = 0; I < 2; ++I)
 #pragma unroll
-        for (int J = 0; J < WT; ++J)
+        for (int J = 0; J < 2; ++J)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t row = i0 + wi * (TILE / 2) + 16 * I + d_row(r, lane);
-                const int64_t col = c0 + wj * (TILE / 2) + 16 * J + d_col(lane);
-                if (row < n && col < cend && row >= col) A[row + col * lda] -= acc[I][J][r];
+                // above the diagonal and past the end: an entry of the triangle, not stored
+                const int64_t row = crow(I) < n ? crow(I) : n - 1, c = ccol(J, r), col = c < row ? c : row;
+                cc[I][J][r] = A[row + col * lda];
+            }
+#pragma unroll
+    for (int I = 0; I < 2; ++I)
+#pragma unroll
+        for (int J = 0; J < 2; ++J) acc[I][J] = cc[I][J] - acc[I][J];
+    if (id == 0) {
+        double *S = smem;
+        const int sb = (int)(cend - t0 < kPanel ? cend - t0 : kPanel);
+#pragma unroll
+        for (int I = 0; I < 2; ++I)
+#pragma unroll
+            for (int J = 0; J < 2; ++J)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = (int)(crow(I) - t0), col = (int)(ccol(J, r) - t0);
+                    S[row * kDiagLd + col] = (row < sb && col <= row) ? acc[I][J][r] : (row == col ? 1.0 : 0.0);
+                }
+        __syncthreads();
+        const int fail = chol_diagonal(S);
+        chol_diagonal_out(S, A, lda, t0, sb, fail, &flag, dinfo);
+        return;
+    }
+#pragma unroll
+    for (int I = 0; I < 2; ++I)
+#pragma unroll
+        for (int J = 0; J < 2; ++J)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t row = crow(I), col = ccol(J, r);
+                if (row < n && col < cend && row >= col) A[row + col * lda] = acc[I][J][r];
             }
 }
 
-template <int TILE>
+// K: a multiple of 16 (whole panels).
 hipError_t update(double *A, int64_t lda, int64_t n, int64_t t0, int64_t cend, int64_t kc, int K,
-                  const int32_t *dinfo, const char *tag, hipStream_t st) {
-    const int64_t Tr = (n - t0 + TILE - 1) / TILE, Tc = (cend - t0 + TILE - 1) / TILE;
+                  int32_t *dinfo, const char *tag, hipStream_t st) {
+    const int64_t Tr = (n - t0 + kPanel - 1) / kPanel, Tc = (cend - t0 + kPanel - 1) / kPanel;
     const int64_t tiles = Tc * Tr - Tc * (Tc - 1) / 2;
     if (tiles <= 0) return hipSuccess;
     if (tiles > INT32_MAX) return hipErrorInvalidValue;
     ProfScope ps(tag, st);
-    hipLaunchKernelGGL(k_chol_update<TILE>, dim3((unsigned)tiles), dim3(256), 0, st, A, lda, n, t0, cend, kc, K,
+    hipLaunchKernelGGL(k_chol_update, dim3((unsigned)tiles), dim3(256), 0, st, A, lda, n, t0, cend, kc, K / 16,
                        Tr, Tc, dinfo);
     return hipGetLastError();
 }
@@ -308,20 +382,25 @@ hipError_t launch_cholesky(int64_t n, double *A, int64_t lda, int32_t *dinfo, hi
     hipLaunchKernelGGL(k_chol_info_clear, dim3(1), dim3(64), 0, st, dinfo);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (n == 0) return hipSuccess;
+    {
+        ProfScope ps("chol_diag", st);
+        hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, A, lda, (int)(n < kPanel ? n : kPanel), dinfo);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     for (int64_t j = 0; j < n; j += kOuter) {
         const int64_t jend = j + kOuter < n ? j + kOuter : n;
         for (int64_t s = j; s < jend; s += kPanel) {
             const int sb = (int)(jend - s < kPanel ? jend - s : kPanel);
-            const int64_t below = n - s - sb;
-            const int64_t grid = below > 0 ? (below + kPanel / 2 - 1) / (kPanel / 2) : 1;
-            {
-                ProfScope ps("chol_panel", st);
-                hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)grid), dim3(kPanel), 0, st, A, lda, n, s, sb, dinfo);
-                e = hipGetLastError();
+            const int64_t below = n - s - sb;   // none unless sb = 64
+            if (below > 0) {
+                ProfScope ps("chol_solve", st);
+                hipLaunchKernelGGL(k_chol_solve, dim3((unsigned)((below + 15) / 16)), dim3(64), 0, st, A, lda, n, s,
+                                   dinfo);
+                if ((e = hipGetLastError()) != hipSuccess) return e;
             }
-            if (e != hipSuccess) return e;
             if (s + sb < jend) {
-                e = update<64>(A, lda, n, s + sb, jend, s, sb, dinfo, "chol_update", st);
+                e = update(A, lda, n, s + sb, jend, s, sb, dinfo, "chol_update", st);
                 if (e != hipSuccess) return e;
             }
         }
@@ -329,7 +408,7 @@ hipError_t launch_cholesky(int64_t n, double *A, int64_t lda, int32_t *dinfo, hi
             // 64 x 64 tiles: four resident workgroups per compute unit hide
             // the operand loads better than 128 x 128 tiles' reuse pays
             // (8192 x 8192: 4.8 against 6.4 ms of trailing updates)
-            e = update<64>(A, lda, n, jend, n, j, (int)(jend - j), dinfo, "chol_syrk", st);
+            e = update(A, lda, n, jend, n, j, (int)(jend - j), dinfo, "chol_syrk", st);
             if (e != hipSuccess) return e;
         }
     }

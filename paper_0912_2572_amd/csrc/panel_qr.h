@@ -194,6 +194,21 @@ template <int K>
 __device__ __forceinline__ void t_term(double &acc, double g, double t) {
     asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(g), "v"(t), "n"(K));
 }
+// u[j] += g(lane j of the 16-lane row) t, j = J0 .. 15.
+template <int J>
+struct RowTerms {
+    __device__ __forceinline__ static void run(double (&u)[16], double g, double t) {
+        if constexpr (J < 16) {
+            t_term<J>(u[J], g, t);
+            RowTerms<J + 1>::run(u, g, t);
+        }
+    }
+};
+template <int J0>
+__device__ __forceinline__ void row_terms(double (&u)[16], double g, double t) {
+    asm("s_nop 1" : "+v"(g));
+    RowTerms<J0>::run(u, g, t);
+}
 template <int J, int K>
 struct TColumn {
     __device__ __forceinline__ static void run(const PanelRegs &pr, double g, double &a0, double &a1) {

@@ -134,24 +134,13 @@ struct SelStep {
     }
 };
 
-// Term K of the unit-lower solve u <- L11^{-1} u: u[j] += (-L11[j][K]) u[K],
-// j > K, with row j of -L11 in lane j of every 16-lane row (column K: nl[K]).
-template <int K, int J>
-struct UnitLowerTerm {
-    __device__ __forceinline__ static void run(double (&u)[16], double nl) {
-        if constexpr (J < 16) {
-            t_term<J>(u[J], nl, u[K]);
-            UnitLowerTerm<K, J + 1>::run(u, nl);
-        }
-    }
-};
+// The unit-lower solve u <- L11^{-1} u, row j of -L11 in lane j of every
+// 16-lane row (column K: nl[K]).
 template <int K>
 struct UnitLowerSolve {
     __device__ __forceinline__ static void run(double (&u)[16], const double (&nl)[16]) {
         if constexpr (K < 15) {
-            double g = nl[K];
-            asm("s_nop 1" : "+v"(g));   // DPP wait states (panel_qr.h, t_term)
-            UnitLowerTerm<K, K + 1>::run(u, g);
+            row_terms<K + 1>(u, nl[K], u[K]);
             UnitLowerSolve<K + 1>::run(u, nl);
         }
     }
