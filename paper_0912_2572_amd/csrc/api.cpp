@@ -916,10 +916,7 @@ TSQR_API int tsqr_block_orth(int64_t m, int64_t nv, const double *V, int64_t ldv
     if (nv > 0) {
         const int iv = (int)nv, ib = (int)b;
         // two passes of block classical Gram-Schmidt
-        TRY(tsqr::launch_proj(V, ldv, iv, W, ldw, ib, m, Hpart, H, ldh, nullptr, 0, st));
-        TRY(tsqr::launch_proj_update(V, ldv, iv, H, ldh, W, ldw, ib, m, st));
-        TRY(tsqr::launch_proj(V, ldv, iv, W, ldw, ib, m, Hpart, H2, nv, H, ldh, st));
-        TRY(tsqr::launch_proj_update(V, ldv, iv, H2, nv, W, ldw, ib, m, st));
+        TRY(tsqr::launch_cgs2(V, ldv, iv, W, ldw, ib, m, Hpart, H, ldh, H2, st));
     }
     // TSQR of the projected block; its thin Q replaces it
     tsqr_factors_s f;
