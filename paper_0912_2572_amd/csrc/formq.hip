@@ -14,9 +14,12 @@
 // The chunk products run as FP64 MFMA tiles in the transposed form
 // Q^T-tile = Z^T V^T, so that every store writes 16 consecutive rows of a
 // column of the column-major Q.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "mfma.h"
+#include "panel_qr.h"
 #include "prof.h"
 
 namespace tsqr {
@@ -183,141 +186,210 @@ __global__ void k_seed_root(double *S, int n, const double *d) {
     }
 }
 
-// Q = -V Z (+ [X; 0] on a first chunk) for the rows of one chunk; wave w
-// takes the 16-row tiles 4 w .. 4 w + 3 of every 256-row block.  The wave
-// keeps its Z operands in registers for the whole chunk and fetches the next
-// two tiles' V while the current tile's products run.
-__device__ __forceinline__ void chunk_out(const FormSmem &sm, const double *__restrict__ Vc, int64_t ldv,
-                                          double *__restrict__ Qc, int64_t ldq, int64_t valid, int n,
-                                          bool first) {
-    const int tid = local_tid(), lane = tid & 63, w = tid >> 6;
-    const int l16 = lane & 15, l4 = lane >> 4;
-    const int kbn = (n + 3) >> 2;
-    double za[16][4];
-#pragma unroll
-    for (int kb = 0; kb < 16; ++kb)
-#pragma unroll
-        for (int CT = 0; CT < 4; ++CT)
-            za[kb][CT] = (kb < kbn) ? sm.Z[(4 * kb + l4) * LD + 16 * CT + l16] : 0.0;
-    auto load_v = [&](int64_t tile, double (&vb)[16]) {
-        const int64_t row = 16 * tile + l16;
-        if (first) {
-#pragma unroll
-            for (int kb = 0; kb < 16; ++kb) {
-                const int col = 4 * kb + l4;
-                double v = 0.0;
-                if (kb < kbn && row < valid && col < n) {
-                    v = Vc[row + (int64_t)col * ldv];
-                    if (row <= col) v = (row == col) ? 1.0 : 0.0;
-                }
-                vb[kb] = v;
-            }
-        } else {
-            // no branch around the loads (so the compiler can keep them in
-            // flight): a row past the chunk reads its last row (that output
-            // row is not stored) and a column past n reads column n - 1 (it
-            // meets a zero row of the padded Z)
-            const int64_t rr = row < valid ? row : valid - 1;
-#pragma unroll
-            for (int kb = 0; kb < 16; ++kb) {
-                const int col = 4 * kb + l4;
-                vb[kb] = Vc[rr + (int64_t)(col < n ? col : n - 1) * ldv];
-            }
-        }
-    };
-    // tiles t, t + 1 (+ 13 past a 4-tile group): two tiles in flight while
-    // one computes, in three buffers whose roles rotate through a 3-way
-    // unrolled loop (no copies of registers whose loads are still in flight)
-    auto next_of = [](int64_t t) { return t + ((t % 4 == 3) ? 13 : 1); };
-    int64_t tile = 4 * w;
-    double ba[16], bb[16], bc[16];
-    if (16 * tile < valid) load_v(tile, ba);
-    if (16 * next_of(tile) < valid) load_v(next_of(tile), bb);
-    auto step = [&](double (&cur)[16], double (&ahead)[16]) {
-        const int64_t t2 = next_of(next_of(tile));
-        if (16 * t2 < valid) load_v(t2, ahead);
-        const int64_t row = 16 * tile + l16;
-        d4 acc[4];
-#pragma unroll
-        for (int CT = 0; CT < 4; ++CT) acc[CT] = d4_zero();
-        // all 16 k-steps, with no branch: past n the Z operand is zero and the
-        // V operand finite, so those products add exact zeros
-#pragma unroll
-        for (int kb = 0; kb < 16; ++kb)
-#pragma unroll
-            for (int CT = 0; CT < 4; ++CT) acc[CT] = mfma_f64(za[kb][CT], cur[kb], acc[CT]);
-        if (!first && n == 64 && 16 * tile + 16 <= valid) {
-            // a whole tile of a later chunk: no guard around the stores
-#pragma unroll
-            for (int CT = 0; CT < 4; ++CT)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    Qc[row + (int64_t)(16 * CT + 4 * r + l4) * ldq] = -acc[CT][r];
-        } else {
-#pragma unroll
-            for (int CT = 0; CT < 4; ++CT)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int col = 16 * CT + 4 * r + l4;
-                    if (row < valid && col < n) {
-                        double val = -acc[CT][r];
-                        if (first && row < n) val += sm.X[row * LD + col];
-                        Qc[row + (int64_t)col * ldq] = val;
-                    }
-                }
-        }
-        tile = next_of(tile);
-    };
-    while (16 * tile < valid) {
-        step(ba, bc);
-        if (16 * tile >= valid) break;
-        step(bb, ba);
-        if (16 * tile >= valid) break;
-        step(bc, bb);
-    }
+// Expansion of a domain's block X through its chunks, last to first, n <= 16 NT
+// columns: eight waves, one workgroup per domain.  Of the n x n products wave w
+// owns row tile w % 4 and the column tiles of half w / 4; X and Z sit in LDS
+// twice (a chunk reads one pair while the next one's are written: one barrier
+// a chunk), X's own tiles in registers as well, T's operand comes from memory a
+// chunk ahead.  Of the output rows wave w owns the 16-row tiles w, w + 8, ...
+// of each chunk, together: an entry of Z read from LDS serves all of them, and
+// the next chunk's V is read into a register as soon as the last product that
+// uses it is issued.
+// What bounds it: at n = 64 the matrix cores (20 thousand cycles a chunk of 256
+// rows) and memory about alike, at small n memory.  Measured against four waves
+// on 64 x 64 products whatever n is, V in flight within a chunk only:
+// 1,048,576 x 64 (256 domains) 0.44 -> 0.32 ms, 1,048,576 x 16 0.25 -> 0.062 ms
+// (4.3 TB/s), 4096 x 16 (4 domains) 0.073 -> 0.013 ms.  A branch per product (skipping T's
+// zeros) or on the first chunk inside the loop cost it a wait each (0.47 ms).
+template <int NT>
+struct FormLeafSmem {
+    double X[2][16 * NT][16 * NT];   // [..][row][form_place]
+    double Z[2][16 * NT][16 * NT];
+};
+// Place of column c in row r: odd rows have the halves of a 32-column span
+// exchanged, so that the two rows a half wave reads fall into different banks.
+template <int NT>
+__device__ __forceinline__ int form_place(int r, int c) {
+    return NT > 1 && 16 * NT % 32 == 0 ? c ^ ((r & 1) << 4) : c;
 }
 
-__global__ __launch_bounds__(256) void k_form_leaf(const double *__restrict__ V, int64_t ldv,
-                                                   const double *__restrict__ Tc,
-                                                   const double *__restrict__ S, PanelArgs pa,
-                                                   double *__restrict__ Q, int64_t ldq) {
+template <int NT>
+__global__ __launch_bounds__(512, 2) void k_form_leaf(const double *__restrict__ V, int64_t ldv,
+                                                      const double *__restrict__ Tc,
+                                                      const double *__restrict__ S, PanelArgs pa,
+                                                      double *__restrict__ Q, int64_t ldq) {
     extern __shared__ double smem_raw[];
-    FormSmem &sm = *reinterpret_cast<FormSmem *>(smem_raw);
+    FormLeafSmem<NT> &sm = *reinterpret_cast<FormLeafSmem<NT> *>(smem_raw);
+    constexpr int NS = NT == 1 ? 1 : (NT == 2 ? 2 : 4);      // the panel's slots
+    constexpr int TPW = chunk_rows(NS) / 128, JH = (NT + 1) / 2;
+    const int w = wave_index<8>(), lane = threadIdx.x & 63, I = w & 3, J0 = (w >> 2) * JH;
+    int l16 = lane & 15, l4 = lane >> 4;
     const int n = pa.n;
-    const int64_t nn = (int64_t)n * n;
-    const int64_t dom = blockIdx.x;
-    const int64_t row0 = dom_row0(pa, dom);
-    const int64_t nrows = dom_rows(pa, dom);
+    const int64_t nn = (int64_t)n * n, dom = blockIdx.x, row0 = dom_row0(pa, dom), nrows = dom_rows(pa, dom);
     const int64_t nch = (nrows + pa.chunk - 1) / pa.chunk;
-    load_nn(sm.X, S + dom * nn, n, n, false);
-    // T of the chunk processed next, fetched one chunk ahead
-    double tn[16];
-    fetch_nn(tn, Tc + (dom_chunk0(pa, dom) + nch - 1) * nn, n, n);
-    for (int64_t ch = nch - 1; ch >= 0; --ch) {
-        const int64_t r0 = row0 + ch * pa.chunk;
-        const int64_t valid = (nrows - ch * pa.chunk < pa.chunk) ? nrows - ch * pa.chunk : pa.chunk;
-        __syncthreads();
-        if (ch > 0) {
-            put_nn(sm.T, tn);
-            fetch_nn(tn, Tc + (dom_chunk0(pa, dom) + ch - 1) * nn, n, n);
-            __syncthreads();
-            lds_gemm64(sm.T, sm.X, sm.Z, LD, true, false, 1.0);    // Z = T_k X
-            __syncthreads();
-            for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) sm.X[e] -= sm.Z[e];
-            // chunk_out reads only Z; X is not read for ch > 0
-            chunk_out(sm, V + r0, ldv, Q + r0, ldq, valid, n, false);
-        } else {
-            load_nn(sm.T, V + r0, ldv, n, true);                     // V_0top (unit lower)
-            __syncthreads();
-            lds_gemm64(sm.T, sm.X, sm.W, LD, true, true, 1.0);     // W = V_0top^T X
-            __syncthreads();
-            put_nn(sm.T, tn);
-            __syncthreads();
-            lds_gemm64(sm.T, sm.W, sm.Z, LD, true, false, 1.0);    // Z = T_0 W
-            __syncthreads();
-            chunk_out(sm, V + r0, ldv, Q + r0, ldq, valid, n, true);
+    const double *T0 = Tc + dom_chunk0(pa, dom) * nn;
+    const bool own = I < NT;
+    V += row0;
+    Q += row0;
+
+    // entries (16 I + l16, 4 kb + l4) of a chunk's T, kb >= 4 I
+    double tk[4 * NT];
+    auto t_ok = [&](int kb) {
+        const int r = 16 * I + l16, c = 4 * kb + l4;
+        return r <= c && c < n;
+    };
+    auto fetch_t = [&](int64_t ch) {
+        const double *T = T0 + ch * nn;
+#pragma unroll
+        for (int kb = 0; kb < 4 * NT; ++kb)
+            tk[kb] = T[t_ok(kb) ? 16 * I + l16 + (4 * kb + l4) * n : 0];
+    };
+    // V of this wave's tiles in a chunk: rows past it repeat its last row,
+    // columns past n column n - 1 (they meet zero rows of Z)
+    double v[TPW][4 * NT];
+    auto fetch_v = [&](int64_t ch, int kb) {
+        const int64_t off = ch * pa.chunk;
+        const int valid = (int)(nrows - off < pa.chunk ? nrows - off : pa.chunk);
+        const double *p = V + off + (int64_t)(4 * kb + l4 < n ? 4 * kb + l4 : n - 1) * ldv;
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+            const int r = 16 * (w + 8 * u) + l16;
+            v[u][kb] = p[r < valid ? r : valid - 1];
         }
-    }
+    };
+    // sum over kb of T's (or V0^T's) operand times M's rows, this wave's tiles
+    // (all of T: no branch, its entries below the diagonal are zeros here)
+    auto product = [&](const double (&a)[4 * NT], const double (&M)[16 * NT][16 * NT], d4 (&z)[JH], auto ok) {
+#pragma unroll
+        for (int j = 0; j < JH; ++j) z[j] = d4_zero();
+#pragma unroll
+        for (int kb = 0; kb < 4 * NT; ++kb) {
+            const double t = ok(kb) ? a[kb] : 0.0;
+#pragma unroll
+            for (int j = 0; j < JH; ++j) {
+                const int J = J0 + j < NT ? J0 + j : NT - 1;
+                z[j] = mfma_f64(t, M[4 * kb + l4][form_place<NT>(4 * kb + l4, 16 * J + l16)], z[j]);
+            }
+        }
+    };
+    auto put = [&](double (&M)[16 * NT][16 * NT], const d4 (&x)[JH]) {
+#pragma unroll
+        for (int j = 0; j < JH; ++j)
+            if (J0 + j < NT) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * I + 4 * r + l4;
+                    M[row][form_place<NT>(row, 16 * (J0 + j) + l16)] = x[j][r];
+                }
+            }
+    };
+
+    fetch_t(nch - 1);
+    d4 x[JH];
+#pragma unroll
+    for (int j = 0; j < JH; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * I + 4 * r + l4, col = 16 * (J0 + j) + l16;
+            const bool ok = row < n && col < n;
+            const double s = S[dom * nn + (ok ? row + col * n : 0)];
+            x[j][r] = ok ? s : 0.0;
+        }
+#pragma unroll
+    for (int kb = 0; kb < 4 * NT; ++kb) fetch_v(nch - 1, kb);
+    if (own) put(sm.X[(nch - 1) & 1], x);
+    __syncthreads();
+    auto chunk = [&](int64_t ch, auto first_) {
+        constexpr bool first = decltype(first_)::value;
+        const int64_t off = ch * pa.chunk;
+        const int valid = (int)(nrows - off < pa.chunk ? nrows - off : pa.chunk);
+        const int cur = (int)(ch & 1);
+        asm volatile("" : "+v"(l16), "+v"(l4));   // addresses are not kept over the loop
+        if constexpr (first) {
+            // W = V0^T X (V0: the unit lower top of the first chunk) in the
+            // free X buffer, then Z = T0 W
+            double vt[4 * NT];
+#pragma unroll
+            for (int kb = 0; kb < 4 * NT; ++kb) {
+                const int r = 4 * kb + l4, c = 16 * I + l16;
+                const double t = V[(r < n && c < n) ? r + (int64_t)c * ldv : 0];
+                vt[kb] = r == c ? 1.0 : t;
+            }
+            if (own) {
+                d4 wv[JH];
+                product(vt, sm.X[cur], wv, [&](int kb) {
+                    const int r = 4 * kb + l4, c = 16 * I + l16;
+                    return r >= c && r < n;
+                });
+                put(sm.X[cur ^ 1], wv);
+            }
+            __syncthreads();
+        }
+        if (own) {
+            d4 z[JH];
+            product(tk, sm.X[first ? cur ^ 1 : cur], z, t_ok);
+            put(sm.Z[cur], z);
+            if constexpr (!first) {
+#pragma unroll
+                for (int j = 0; j < JH; ++j) x[j] -= z[j];
+                put(sm.X[cur ^ 1], x);
+            }
+        }
+        if constexpr (!first) fetch_t(ch - 1);
+        __syncthreads();
+        // Q = -V Z, plus [X; 0] on a first chunk
+        if constexpr (first) {
+#pragma unroll
+            for (int u = 0; u < TPW; ++u) {
+                const int r = 16 * (w + 8 * u) + l16;
+#pragma unroll
+                for (int kb = 0; kb < 4 * NT; ++kb) {
+                    const int c = 4 * kb + l4;
+                    v[u][kb] = r > c ? v[u][kb] : (r == c ? 1.0 : 0.0);
+                }
+            }
+        }
+        d4 acc[TPW][NT];
+#pragma unroll
+        for (int u = 0; u < TPW; ++u)
+#pragma unroll
+            for (int c = 0; c < NT; ++c) acc[u][c] = d4_zero();
+#pragma unroll
+        for (int kb = 0; kb < 4 * NT; ++kb) {
+#pragma unroll
+            for (int c = 0; c < NT; ++c) {
+                const double z = sm.Z[cur][4 * kb + l4][form_place<NT>(4 * kb + l4, 16 * c + l16)];
+#pragma unroll
+                for (int u = 0; u < TPW; ++u) acc[u][c] = mfma_f64(z, v[u][kb], acc[u][c]);
+            }
+            if constexpr (!first) fetch_v(ch - 1, kb);
+        }
+        const bool whole = !first && valid == (int)pa.chunk && n == 16 * NT;   // no guard around the stores
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+            const int r = 16 * (w + 8 * u) + l16;
+            double *q = Q + off + r + l4 * ldq;
+            if (whole) {
+#pragma unroll
+                for (int c = 0; c < NT; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) q[(int64_t)(16 * c + 4 * i) * ldq] = -acc[u][c][i];
+            } else if (r < valid) {
+#pragma unroll
+                for (int c = 0; c < NT; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int col = 16 * c + 4 * i + l4;
+                        double o = -acc[u][c][i];
+                        if (first && r < n) o += sm.X[cur][r][form_place<NT>(r, col)];
+                        if (col < n) q[(int64_t)(16 * c + 4 * i) * ldq] = o;
+                    }
+            }
+        }
+    };
+#pragma unroll 1
+    for (int64_t ch = nch - 1; ch > 0; --ch) chunk(ch, std::false_type{});
+    chunk(0, std::true_type{});
 }
 
 static hipError_t set_smem(const void *k) {
@@ -352,14 +424,26 @@ hipError_t launch_tree_down(const double *Rdom, const double *Tnode, double *S, 
     return hipGetLastError();
 }
 
-hipError_t launch_form_leaf(const double *V, int64_t ldv, const double *Tc, const double *S,
-                            const PanelArgs &pa, double *Q, int64_t ldq, hipStream_t st) {
-    hipError_t e = set_smem((const void *)k_form_leaf);
+template <int NT>
+static hipError_t form_leaf(const double *V, int64_t ldv, const double *Tc, const double *S, const PanelArgs &pa,
+                            double *Q, int64_t ldq, hipStream_t st) {
+    const size_t sh = sizeof(FormLeafSmem<NT>);
+    hipError_t e = hipFuncSetAttribute((const void *)k_form_leaf<NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)sh);
     if (e != hipSuccess) return e;
     ProfScope ps("form_leaf", st);
-    hipLaunchKernelGGL(k_form_leaf, dim3((unsigned)pa.P), dim3(256), sizeof(FormSmem), st, V, ldv, Tc, S,
-                       pa, Q, ldq);
+    hipLaunchKernelGGL(k_form_leaf<NT>, dim3((unsigned)pa.P), dim3(512), sh, st, V, ldv, Tc, S, pa, Q, ldq);
     return hipGetLastError();
+}
+
+hipError_t launch_form_leaf(const double *V, int64_t ldv, const double *Tc, const double *S,
+                            const PanelArgs &pa, double *Q, int64_t ldq, hipStream_t st) {
+    switch ((pa.n + 15) >> 4) {
+        case 1: return form_leaf<1>(V, ldv, Tc, S, pa, Q, ldq, st);
+        case 2: return form_leaf<2>(V, ldv, Tc, S, pa, Q, ldq, st);
+        case 3: return form_leaf<3>(V, ldv, Tc, S, pa, Q, ldq, st);
+        default: return form_leaf<4>(V, ldv, Tc, S, pa, Q, ldq, st);
+    }
 }
 
 }  // namespace tsqr
