@@ -50,30 +50,4 @@ struct TileF32 {
 __device__ __forceinline__ int d_row(int r, int lane) { return 4 * r + (lane >> 4); }
 __device__ __forceinline__ int d_col(int lane) { return lane & 15; }
 
-// C = op(A) * B for 64 x 64 row-major LDS matrices (row stride ld),
-// computed by the 4 waves of a 256-thread workgroup: wave w produces the
-// 16-row block w of C.  `a_upper` skips the zero blocks of an upper-
-// triangular A.  If transA, op(A) = A^T.  C may not alias A or B.
-__device__ __forceinline__ void lds_gemm64(const double *A, const double *B, double *C, int ld,
-                                           bool a_upper, bool transA, double scale) {
-    const int tid = local_tid(), lane = tid & 63, w = tid >> 6;
-    const int I = w;
-    d4 acc[4];
-#pragma unroll
-    for (int J = 0; J < 4; ++J) acc[J] = d4_zero();
-    // op(A) upper triangular: blocks K < I vanish
-    const int kb0 = a_upper ? 4 * I : 0;
-    for (int kb = kb0; kb < 16; ++kb) {
-        const int i = 16 * I + (lane & 15), k = 4 * kb + (lane >> 4);
-        const double a = transA ? A[k * ld + i] : A[i * ld + k];
-#pragma unroll
-        for (int J = 0; J < 4; ++J) acc[J] = mfma_f64(a, B[k * ld + 16 * J + (lane & 15)], acc[J]);
-    }
-#pragma unroll
-    for (int J = 0; J < 4; ++J)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            C[(16 * I + d_row(r, lane)) * ld + 16 * J + d_col(lane)] = scale * acc[J][r];
-}
-
 }  // namespace tsqr
