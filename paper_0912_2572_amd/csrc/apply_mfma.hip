@@ -30,43 +30,6 @@ namespace tsqr {
 
 constexpr int KBM = 16;   // most columns of B of the three-pass form
 
-// V element of a chunk with the implicit unit diagonal of a first chunk.
-template <typename VT>
-__device__ __forceinline__ VT v_elem(const VT *__restrict__ Vc, int64_t ldv, int64_t row, int col,
-                                     int64_t valid, int n, bool first) {
-    if (row >= valid || col >= n) return VT(0);
-    if (first && row <= col) return (row == col) ? VT(1) : VT(0);
-    return Vc[row + (int64_t)col * ldv];
-}
-
-// Four consecutive entries p[0..3] as 16-byte loads (p 16-byte aligned),
-// or zeros when !ok; FP64 reads two double2, FP32 one float4, and the
-// entries are converted to T.
-template <typename T, typename S>
-__device__ __forceinline__ void load4(const S *__restrict__ p, bool ok, T (&v)[4]) {
-    if constexpr (sizeof(S) == 8) {
-        double2 x0 = {0.0, 0.0}, x1 = {0.0, 0.0};
-        if (ok) {
-            x0 = reinterpret_cast<const double2 *>(p)[0];
-            x1 = reinterpret_cast<const double2 *>(p)[1];
-        }
-        v[0] = T(x0.x); v[1] = T(x0.y); v[2] = T(x1.x); v[3] = T(x1.y);
-    } else {
-        float4 x = {0.f, 0.f, 0.f, 0.f};
-        if (ok) x = *reinterpret_cast<const float4 *>(p);
-        v[0] = T(x.x); v[1] = T(x.y); v[2] = T(x.z); v[3] = T(x.w);
-    }
-}
-
-// A wave's row range [r, r + rows) of V and B can be read 4 rows at a time
-// with 16-byte loads: whole 16-row blocks, every column start 16-byte aligned.
-template <typename VT>
-__device__ __forceinline__ bool wide_rows_ok(const VT *v, int64_t ldv, const double *b, int64_t ldb, int64_t rows) {
-    return rows > 0 && rows % 16 == 0 && (reinterpret_cast<uintptr_t>(v) & 15) == 0 &&
-           (reinterpret_cast<uintptr_t>(b) & 15) == 0 && (ldv * (int64_t)sizeof(VT)) % 16 == 0 &&
-           (ldb * 8) % 16 == 0;
-}
-
 // ---------------------------------------------------------------------------
 // Chained leaf apply: one workgroup per domain and block of 16 NB columns walks
 // the domain's chunks.  A wave owns a quarter of each chunk's rows.  Its rows of
@@ -577,53 +540,87 @@ constexpr size_t vtb_lds_bytes(int64_t kc) {
     return (size_t)4 * 64 * (size_t)kc * sizeof(typename Tile::T);
 }
 
-template <typename Tile>
+// Four consecutive rows of a column, at any alignment of the element's.
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void load_rows4(const double *__restrict__ p, double (&v)[4]) {
+    const d2u a = *reinterpret_cast<const d2u *>(p), b = *reinterpret_cast<const d2u *>(p + 2);
+    v[0] = a.x;
+    v[1] = a.y;
+    v[2] = b.x;
+    v[3] = b.y;
+}
+__device__ __forceinline__ void load_rows4(const float *__restrict__ p, float (&v)[4]) {
+    const f4u a = *reinterpret_cast<const f4u *>(p);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = a[q];
+}
+
+// n <= 16 NT.  A lane reads 4 consecutive rows of its column (16 rows x 16
+// columns per load); MFMA q takes row 4 l4 + q of the block as its k = l4
+// element.  Two blocks' loads go out together, with no condition on them:
+// columns past the last repeat it (their products are dropped), and so do
+// rows, against zeros of B.  What bounds it: reading V.  With loads that needed
+// 16-byte column starts (element loads elsewhere) and a condition each, odd
+// heights ran at a quarter of the rate: 32 mixed matrices of 1,000 to 200,000
+// rows 350 -> 150 us, 1,048,576 x 64 FP32 66 -> 60 us.
+template <typename Tile, int NT>
 __device__ __forceinline__ void chunk_vtb(VtbSmem<Tile> &sm, const typename Tile::T *__restrict__ Vc,
                                           int64_t ldv, const double *__restrict__ Bc, int64_t ldb,
-                                          int64_t rlo, int64_t valid, int n, int kc, bool first) {
+                                          int rlo, int valid, int n, int kc) {
     using T = typename Tile::T;
     using Acc = typename Tile::Acc;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int l16 = lane & 15, l4 = lane >> 4;
-    const int mtn = (n + 15) >> 4;
-    Acc acc[4];
+    const int lane = threadIdx.x & 63, w = wave_index<4>(), l16 = lane & 15, l4 = lane >> 4;
+    Acc acc[NT];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) acc[mt] = Acc{0, 0, 0, 0};
-    const int64_t span = valid - rlo;
-    const int64_t per = ((span + 15) / 16 + 3) / 4 * 16;
-    const int64_t lo = rlo + w * per, hi = (lo + per < valid) ? lo + per : valid;
-    if (wide_rows_ok(Vc + lo, ldv, Bc + lo, ldb, hi - lo)) {
-        // each lane reads 4 consecutive rows of its column with 16-byte
-        // loads (16 rows x 16 columns per instruction); MFMA q takes row
-        // 4 l4 + q of the 16-row block as its k = l4 element
-        for (int64_t r16 = lo; r16 < hi; r16 += 16) {
-            const int64_t rb = r16 + 4 * l4;
-            T b4[4];
-            load4<T>(Bc + rb + (int64_t)l16 * ldb, l16 < kc, b4);
+    for (int mt = 0; mt < NT; ++mt) acc[mt] = Acc{0, 0, 0, 0};
+    const int span = valid - rlo, per = ((span + 15) / 16 + 3) / 4 * 16;
+    const int lo = rlo + w * per, hi = (lo + per < valid) ? lo + per : valid;
+    const double *bp = Bc + (int64_t)(l16 < kc ? l16 : kc - 1) * ldb;
+    const T *vp[NT];
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                if (mt >= mtn) break;
-                T a4[4];
-                load4<T>(Vc + rb + (int64_t)(16 * mt + l16) * ldv, 16 * mt + l16 < n, a4);
+    for (int mt = 0; mt < NT; ++mt) vp[mt] = Vc + (int64_t)(16 * mt + l16 < n ? 16 * mt + l16 : n - 1) * ldv;
+    int r16 = lo;
+#pragma unroll 1
+    for (; r16 + 32 <= hi; r16 += 32) {
+        double b[2][4];
+        T a[2][NT][4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[mt] = Tile::mfma(a4[q], b4[q], acc[mt]);
-            }
+        for (int u = 0; u < 2; ++u) {
+            const int rb = r16 + 16 * u + 4 * l4;
+            load_rows4(bp + rb, b[u]);
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt) load_rows4(vp[mt] + rb, a[u][mt]);
         }
-    } else {
-        for (int64_t r4 = lo; r4 < hi; r4 += 4) {
-            const int64_t row = r4 + l4;
-            const T b = T((row < hi && l16 < kc) ? Bc[row + (int64_t)l16 * ldb] : 0.0);
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                if (mt >= mtn) break;
-                const T a = (row < hi) ? v_elem<T>(Vc, ldv, row, 16 * mt + l16, valid, n, first) : T(0);
-                acc[mt] = Tile::mfma(a, b, acc[mt]);
-            }
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int mt = 0; mt < NT; ++mt) acc[mt] = Tile::mfma(a[u][mt][q], T(b[u][q]), acc[mt]);
+    }
+#pragma unroll 1
+    for (; r16 < hi; r16 += 16) {
+        double b[4];
+        T a[NT][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = r16 + 4 * l4 + q, rc = r < hi ? r : hi - 1;
+            b[q] = bp[rc];
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt) a[mt][q] = vp[mt][rc];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const T x = r16 + 4 * l4 + q < hi ? T(b[q]) : T(0);
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt) acc[mt] = Tile::mfma(a[mt][q], x, acc[mt]);
         }
     }
     if (l16 < kc) {
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+        for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) sm.Wp[(64 * w + 16 * mt + Tile::drow(r, lane)) * kc + l16] = acc[mt][r];
     }
@@ -643,8 +640,16 @@ __device__ __forceinline__ void apply_p1_body(const typename Tile::T *__restrict
     if (ch >= nch) return;
     const int kc = (int)k;
     const int64_t r0 = row0 + ch * pa.chunk;
-    const int64_t valid = (nrows - ch * pa.chunk < pa.chunk) ? nrows - ch * pa.chunk : pa.chunk;
-    chunk_vtb<Tile>(sm, V + r0, ldv, B + r0, ldb, ch == 0 ? n : 0, valid, n, kc, ch == 0);
+    const int valid = (int)((nrows - ch * pa.chunk < pa.chunk) ? nrows - ch * pa.chunk : pa.chunk);
+    auto vtb = [&](auto nt) {
+        chunk_vtb<Tile, decltype(nt)::value>(sm, V + r0, ldv, B + r0, ldb, ch == 0 ? n : 0, valid, n, kc);
+    };
+    switch ((n + 15) >> 4) {
+        case 1: vtb(std::integral_constant<int, 1>{}); break;
+        case 2: vtb(std::integral_constant<int, 2>{}); break;
+        case 3: vtb(std::integral_constant<int, 3>{}); break;
+        default: vtb(std::integral_constant<int, 4>{});
+    }
     // P_c = the four waves' partials added in wave order
     using T = typename Tile::T;
     double *P = Pc + (dom_chunk0(pa, dom) + ch) * (int64_t)n * k;
@@ -663,196 +668,249 @@ __global__ __launch_bounds__(256) void k_apply_p1(const typename Tile::T *__rest
     apply_p1_body<Tile>(V, ldv, pa, B, ldb, k, Pc, blockIdx.y, blockIdx.x);
 }
 
+template <int NT>
 struct ChainSmem {
-    double Tm[64 * kLdsStride];
-    // unit lower V_0top of the first chunk, its lower triangle (diagonal of
-    // ones included) packed by rows: entry (r, c), c <= r, at r (r + 1) / 2 + c.
-    // Packed, the struct fits two workgroups in a CU's LDS.
-    double V0[64 * 65 / 2];
-    double Y[64][KBM];
-    double W[64][KBM];
-    double Z[64][KBM];
+    double W[2][16 * NT][KBM];
+    double Z[16 * NT][KBM];
 };
-static_assert(2 * sizeof(ChainSmem) <= 160 * 1024, "two chain workgroups per CU");
-__device__ __forceinline__ int v0_at(int r, int c) { return r * (r + 1) / 2 + c; }
 
-// Pass 2 for one domain (FP64).
+// Pass 2 for one domain (FP64), n <= 16 NT: wave w owns rows 16 w .. 16 w + 15
+// of Y (in registers for the whole chain), W and Z; T's operand and P_c come
+// from memory a chunk ahead, W crosses the waves through LDS (two buffers:
+// one barrier a chunk).  What bounds it: the chain -- per chunk 16 dependent
+// matrix-core tiles of 64 cycles and the barrier -- and reading T.  Measured at 16 chunks of 64
+// columns: 81 -> 45 us, against dot products of up to 64 terms per thread.
+template <bool QT, int NT>
+__device__ __forceinline__ void apply_p2_chain(ChainSmem<NT> &sm, const double *__restrict__ V64,
+                                               const float *__restrict__ V32, int64_t ldv,
+                                               const double *__restrict__ Tc, const PanelArgs &pa,
+                                               double *__restrict__ B, int64_t ldb, int64_t k,
+                                               const double *__restrict__ Pc, double *__restrict__ Zc, int64_t dom) {
+    const int n = pa.n, kc = (int)k;
+    const int w = wave_index<4>(), lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+    const int64_t nn = (int64_t)n * n, row0 = dom_row0(pa, dom), nrows = dom_rows(pa, dom);
+    const int64_t nch = (nrows + pa.chunk - 1) / pa.chunk;
+    const double *T0 = Tc + dom_chunk0(pa, dom) * nn;
+    const double *P0 = Pc + dom_chunk0(pa, dom) * (int64_t)n * k;
+    double *Z0 = Zc + dom_chunk0(pa, dom) * (int64_t)n * k;
+    const bool own = w < NT, colok = l16 < kc;
+    const int col = colok ? l16 : 0;
+    auto row_of = [&](int r) { return 16 * w + 4 * r + l4; };
+    // op(T)'s entry kb of this lane: (4 kb + l4, 16 w + l16) or, for Q, its transpose's place
+    auto t_at = [&](int kb, bool &ok) {
+        const int i = 16 * w + l16, q = 4 * kb + l4, r = QT ? q : i, c = QT ? i : q;
+        ok = r <= c && c < n;
+        return ok ? r + c * n : 0;
+    };
+    // V_0top's entry (r, c), unit lower triangular
+    auto v0 = [&](int r, int c) {
+        const bool ok = c < r && r < n;
+        const int64_t at = row0 + (ok ? r + (int64_t)c * ldv : 0);
+        const double v = V32 ? (double)V32[at] : V64[at];
+        return r == c ? 1.0 : (ok ? v : 0.0);
+    };
+    // T's operand and P_c of the next chunk
+    double tn[4 * NT];
+    d4 pn;
+    auto fetch = [&](int64_t ch) {
+#pragma unroll
+        for (int kb = 0; kb < 4 * NT; ++kb) {
+            bool ok;
+            tn[kb] = T0[ch * nn + t_at(kb, ok)];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            pn[r] = P0[ch * (int64_t)n * k + (row_of(r) < n ? row_of(r) : 0) + (int64_t)col * n];
+    };
+    auto chunk_of_step = [&](int64_t s) {   // past the chain: its last chunk again (not used)
+        s = s < nch ? s : nch - 1;
+        return QT ? s : nch - 1 - s;
+    };
+    fetch(chunk_of_step(0));
+    d4 y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double v = B[row0 + (row_of(r) < n ? row_of(r) : 0) + (int64_t)col * ldb];
+        y[r] = (colok && row_of(r) < n) ? v : 0.0;
+    }
+    // step s: `add` to P_c gives W, then Z = op(T) W
+    auto zed = [&](int64_t s, const d4 &add) {
+        const int64_t ch = chunk_of_step(s);
+        double(*W)[KBM] = sm.W[s & 1];
+        double t[4 * NT];
+#pragma unroll
+        for (int kb = 0; kb < 4 * NT; ++kb) {
+            bool ok;
+            t_at(kb, ok);
+            t[kb] = ok ? tn[kb] : 0.0;
+        }
+        if (own) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) W[row_of(r)][l16] = row_of(r) < n ? (colok ? pn[r] : 0.0) + add[r] : 0.0;
+        }
+        fetch(chunk_of_step(s + 1));
+        __syncthreads();
+        d4 z = d4_zero();
+        if (own) {
+#pragma unroll
+            for (int kb = 0; kb < 4 * NT; ++kb) z = mfma_f64(t[kb], W[4 * kb + l4][l16], z);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (colok && row_of(r) < n) Z0[ch * (int64_t)n * k + row_of(r) + (int64_t)col * n] = z[r];
+        }
+        return z;
+    };
+    // the first chunk: W = V_0top^T Y + P, Y <- Y - V_0top Z
+    auto first = [&](int64_t s) {
+        d4 acc = d4_zero();
+        if (own) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sm.Z[row_of(r)][l16] = y[r];
+        }
+        __syncthreads();
+        if (own) {
+            double a[4 * NT];
+#pragma unroll
+            for (int kb = 0; kb < 4 * NT; ++kb) a[kb] = v0(4 * kb + l4, 16 * w + l16);
+#pragma unroll
+            for (int kb = 0; kb < 4 * NT; ++kb) acc = mfma_f64(a[kb], sm.Z[4 * kb + l4][l16], acc);
+        }
+        const d4 z = zed(s, acc);
+        if (own) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sm.Z[row_of(r)][l16] = z[r];
+        }
+        __syncthreads();
+        if (own) {
+            double a[4 * NT];
+#pragma unroll
+            for (int kb = 0; kb < 4 * NT; ++kb) a[kb] = v0(16 * w + l16, 4 * kb + l4);
+            acc = d4_zero();
+#pragma unroll
+            for (int kb = 0; kb < 4 * NT; ++kb) acc = mfma_f64(a[kb], sm.Z[4 * kb + l4][l16], acc);
+            y -= acc;
+        }
+    };
+    if constexpr (QT) first(0);
+#pragma unroll 1
+    for (int64_t s = QT ? 1 : 0; s < (QT ? nch : nch - 1); ++s) y -= zed(s, y);
+    if constexpr (!QT) first(nch - 1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (colok && row_of(r) < n) B[row0 + row_of(r) + (int64_t)col * ldb] = y[r];
+}
+
+template <bool QT>
 __device__ __forceinline__ void apply_p2_body(const double *__restrict__ V64, const float *__restrict__ V32,
                                               int64_t ldv, const double *__restrict__ Tc, const PanelArgs &pa,
-                                              double *__restrict__ B, int64_t ldb, int64_t k, int trans,
-                                              const double *__restrict__ Pc, double *__restrict__ Zc,
-                                              int64_t dom) {
-    extern __shared__ double smem_raw[];
-    ChainSmem &sm = *reinterpret_cast<ChainSmem *>(smem_raw);
-    const int n = pa.n, kc = (int)k, tid = threadIdx.x;
-    const int64_t nn = (int64_t)n * n;
-    const int64_t row0 = dom_row0(pa, dom);
-    const int64_t nrows = dom_rows(pa, dom);
-    const int64_t nch = (nrows + pa.chunk - 1) / pa.chunk;
-    for (int e = tid; e < 64 * KBM; e += 256) {
-        const int r = e >> 4, c = e & 15;
-        sm.Y[r][c] = (r < n && c < kc) ? B[row0 + r + (int64_t)c * ldb] : 0.0;
-    }
-    // V_0top, unit lower triangular (the reflector storage precision)
-    for (int e = tid; e < 64 * 64; e += 256) {
-        const int r = e & 63, q = e >> 6;
-        if (q > r) continue;
-        double v = 0.0;
-        if (r < n && q < n) {
-            if (r == q) v = 1.0;
-            else v = V32 ? (double)V32[row0 + r + (int64_t)q * ldv] : V64[row0 + r + (int64_t)q * ldv];
-        }
-        sm.V0[v0_at(r, q)] = v;
-    }
-    // Only the n x kc live entries are computed (e < n kc: i = e % n, j = e / n).
-    // The next chunk's T and P_c are fetched into registers while the current
-    // chunk is processed (loads retire in order, so a P_c loaded inside the
-    // step would also wait for the T fetched ahead).
-    const int live = n * kc;
-    constexpr int kTPer = 64 * 64 / 256;    // T entries per thread
-    constexpr int kPPer = 64 * KBM / 256;   // P_c entries per thread (live <= 64 KBM)
-    double tnext[kTPer], pnext[kPPer];
-    auto fetch_t = [&](int64_t ch) {
-        const double *Tk = Tc + (dom_chunk0(pa, dom) + ch) * nn;
-#pragma unroll
-        for (int u = 0; u < kTPer; ++u) {
-            const int e = tid + 256 * u, r = e & 63, q = e >> 6;
-            tnext[u] = (r < n && q < n) ? Tk[r + (int64_t)q * n] : 0.0;
-        }
-        // P_c is n x kc, column-major with ld n: entry (e % n, e / n) at e
-        const double *P = Pc + (dom_chunk0(pa, dom) + ch) * (int64_t)n * k;
-#pragma unroll
-        for (int u = 0; u < kPPer; ++u) {
-            const int e = tid + 256 * u;
-            pnext[u] = (e < live) ? P[e] : 0.0;
-        }
+                                              double *__restrict__ B, int64_t ldb, int64_t k,
+                                              const double *__restrict__ Pc, double *__restrict__ Zc, int64_t dom) {
+    __shared__ ChainSmem<4> sm;
+    auto run = [&](auto nt) {
+        constexpr int NT = decltype(nt)::value;
+        apply_p2_chain<QT, NT>(reinterpret_cast<ChainSmem<NT> &>(sm), V64, V32, ldv, Tc, pa, B, ldb, k, Pc, Zc, dom);
     };
-    auto chunk_step = [&](int64_t ch, int64_t ch_next) {
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kTPer; ++u) {
-            const int e = tid + 256 * u, r = e & 63, q = e >> 6;
-            sm.Tm[r * kLdsStride + q] = tnext[u];
-        }
-        double pcur[kPPer];
-#pragma unroll
-        for (int u = 0; u < kPPer; ++u) pcur[u] = pnext[u];
-        if (ch_next >= 0) fetch_t(ch_next);
-        // W = (V_0top^T Y on a first chunk, else Y) + P_c
-#pragma unroll
-        for (int u = 0; u < kPPer; ++u) {
-            const int e = tid + 256 * u;
-            if (e >= live) continue;
-            const int m = e % n, j = e / n;
-            double wv = 0.0;
-            if (ch == 0) {
-                for (int r = m; r < n; ++r) wv = fma(sm.V0[v0_at(r, m)], sm.Y[r][j], wv);
-            } else {
-                wv = sm.Y[m][j];
-            }
-            sm.W[m][j] = wv + pcur[u];
-        }
-        __syncthreads();
-        for (int e = tid; e < live; e += 256) {
-            const int i = e % n, j = e / n;
-            double z = 0.0;
-            if (trans) {
-                for (int q = 0; q <= i; ++q) z = fma(sm.Tm[q * kLdsStride + i], sm.W[q][j], z);
-            } else {
-                for (int q = i; q < n; ++q) z = fma(sm.Tm[i * kLdsStride + q], sm.W[q][j], z);
-            }
-            sm.Z[i][j] = z;
-            Zc[(dom_chunk0(pa, dom) + ch) * (int64_t)n * k + i + (int64_t)j * n] = z;
-        }
-        __syncthreads();
-        // Y <- Y - Z, or on a first chunk Y <- Y - V_0top Z
-        for (int e = tid; e < live; e += 256) {
-            const int i = e % n, j = e / n;
-            if (ch == 0) {
-                double u = 0.0;
-                for (int q = 0; q <= i; ++q) u = fma(sm.V0[v0_at(i, q)], sm.Z[q][j], u);
-                sm.W[i][j] = sm.Y[i][j] - u;
-            } else {
-                sm.Y[i][j] -= sm.Z[i][j];
-            }
-        }
-        if (ch == 0) {
-            __syncthreads();
-            for (int e = tid; e < live; e += 256) {
-                const int i = e % n, j = e / n;
-                sm.Y[i][j] = sm.W[i][j];
-            }
-        }
-    };
-    if (trans) {
-        fetch_t(0);
-        for (int64_t ch = 0; ch < nch; ++ch) chunk_step(ch, ch + 1 < nch ? ch + 1 : -1);
-    } else {
-        fetch_t(nch - 1);
-        for (int64_t ch = nch - 1; ch >= 0; --ch) chunk_step(ch, ch - 1);
-    }
-    __syncthreads();
-    for (int e = tid; e < 64 * KBM; e += 256) {
-        const int r = e >> 4, c = e & 15;
-        if (r < n && c < kc) B[row0 + r + (int64_t)c * ldb] = sm.Y[r][c];
+    switch ((pa.n + 15) >> 4) {
+        case 1: run(std::integral_constant<int, 1>{}); break;
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        default: run(std::integral_constant<int, 4>{});
     }
 }
 
+template <bool QT>
 __global__ __launch_bounds__(256) void k_apply_p2(const double *__restrict__ V64, const float *__restrict__ V32,
                                                   int64_t ldv, const double *__restrict__ Tc, PanelArgs pa,
-                                                  double *__restrict__ B, int64_t ldb, int64_t k, int trans,
+                                                  double *__restrict__ B, int64_t ldb, int64_t k,
                                                   const double *__restrict__ Pc, double *__restrict__ Zc) {
-    apply_p2_body(V64, V32, ldv, Tc, pa, B, ldb, k, trans, Pc, Zc, blockIdx.x);
+    apply_p2_body<QT>(V64, V32, ldv, Tc, pa, B, ldb, k, Pc, Zc, blockIdx.x);
 }
 
 // Pass 3: B_c <- B_c - V_c Z_c over the chunk's rows (a first chunk from
-// row n on), transposed MFMA form as in chunk_apply_m; the Z operand stays in
-// registers, so the kernel needs no LDS and many workgroups share a CU.
+// row n on), transposed: a product tile's columns are 16 rows of B.  A lane
+// reads two consecutive rows of V (32 rows x 4 columns per load), one for each
+// of two tiles; the Z operand stays in registers, so the kernel needs no LDS
+// and many workgroups share a CU.  The loads are unconditional: columns past
+// the last repeat it and meet zeros of Z, a pair of rows past the end moves
+// back to the last two.  What bounds it: reading V.  Against one row a lane and
+// a condition on each load: 32 mixed matrices of 1,000 to 200,000 rows 235 ->
+// 155 us, 1,048,576 x 64 FP64 134 -> 120 us.
+template <typename T>
+struct RowPair;
+template <>
+struct RowPair<double> { using V = d2u; };
+template <>
+struct RowPair<float> { using V = f2u; };
+
+template <typename Tile, int NT>
+__device__ __forceinline__ void chunk_minus_vz(const typename Tile::T *__restrict__ Vc, int64_t ldv,
+                                               double *__restrict__ Bc, int64_t ldb, const double *__restrict__ Z,
+                                               int64_t r0, int lo, int valid, int n, int kc) {
+    using T = typename Tile::T;
+    using Acc = typename Tile::Acc;
+    using Pair = typename RowPair<T>::V;
+    const int lane = threadIdx.x & 63, w = wave_index<4>(), l16 = lane & 15, l4 = lane >> 4;
+    // A[i][q] = Z^T[col i][reflector q] for q = 4 kb + l4
+    T za[4 * NT];
+#pragma unroll
+    for (int kb = 0; kb < 4 * NT; ++kb) {
+        const int q = 4 * kb + l4;
+        const bool ok = q < n && l16 < kc;
+        const double z = Z[ok ? q + l16 * n : 0];
+        za[kb] = ok ? T(z) : T(0);
+    }
+#pragma unroll 1
+    for (int t0 = 32 * w; t0 < valid; t0 += 128) {
+        const int R = t0 + 2 * l16;
+        int Rc = R < valid - 2 ? R : valid - 2;
+        if (r0 == 0 && Rc < 0) Rc = 0;   // one row in all: the pair's second is not used
+        const T *vp = Vc + Rc;
+        Pair v[4 * NT];
+#pragma unroll
+        for (int kb = 0; kb < 4 * NT; ++kb)
+            v[kb] = *reinterpret_cast<const Pair *>(vp + (int64_t)(4 * kb + l4 < n ? 4 * kb + l4 : n - 1) * ldv);
+        Acc acc[2] = {Acc{0, 0, 0, 0}, Acc{0, 0, 0, 0}};
+        if (Rc != R) {   // a moved pair's second row is row R, where there is one
+#pragma unroll
+            for (int kb = 0; kb < 4 * NT; ++kb) v[kb].x = v[kb].y;
+        }
+#pragma unroll
+        for (int kb = 0; kb < 4 * NT; ++kb) {
+            acc[0] = Tile::mfma(za[kb], v[kb].x, acc[0]);
+            acc[1] = Tile::mfma(za[kb], v[kb].y, acc[1]);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int col = Tile::drow(r, lane);
+            if (col < kc) {
+                double *p = Bc + R + (int64_t)col * ldb;
+                if (R >= lo && R < valid) p[0] -= (double)acc[0][r];
+                if (R + 1 >= lo && R + 1 < valid) p[1] -= (double)acc[1][r];
+            }
+        }
+    }
+}
+
 template <typename Tile>
 __device__ __forceinline__ void apply_p3_body(const typename Tile::T *__restrict__ V, int64_t ldv,
                                               const PanelArgs &pa, double *__restrict__ B, int64_t ldb, int64_t k,
                                               const double *__restrict__ Zc, int64_t dom, int64_t ch) {
-    using T = typename Tile::T;
-    using Acc = typename Tile::Acc;
     const int n = pa.n, kc = (int)k;
     const int64_t row0 = dom_row0(pa, dom);
     const int64_t nrows = dom_rows(pa, dom);
     const int64_t nch = (nrows + pa.chunk - 1) / pa.chunk;
     if (ch >= nch) return;
     const int64_t r0 = row0 + ch * pa.chunk;
-    const int64_t valid = (nrows - ch * pa.chunk < pa.chunk) ? nrows - ch * pa.chunk : pa.chunk;
-    const bool first = ch == 0;
+    const int valid = (int)((nrows - ch * pa.chunk < pa.chunk) ? nrows - ch * pa.chunk : pa.chunk);
     const double *Z = Zc + (dom_chunk0(pa, dom) + ch) * (int64_t)n * k;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int l16 = lane & 15, l4 = lane >> 4;
-    const int kbn = (n + 3) >> 2;
-    // A[i][q] = Z^T[col i][reflector q] for q = 4 kb + l4
-    T za[16];
-#pragma unroll
-    for (int kb = 0; kb < 16; ++kb) {
-        const int q = 4 * kb + l4;
-        za[kb] = (q < n && l16 < kc) ? T(Z[q + (int64_t)l16 * n]) : T(0);
-    }
-    const T *Vc = V + r0;
-    double *Bc = B + r0;
-    for (int64_t t0 = 16 * w; t0 < valid; t0 += 64) {
-        const int64_t row = t0 + l16;
-        const bool live = row < valid && !(first && row < n);
-        T vv[16];
-#pragma unroll
-        for (int kb = 0; kb < 16; ++kb)
-            vv[kb] = (kb < kbn && live) ? v_elem<T>(Vc, ldv, row, 4 * kb + l4, valid, n, first) : T(0);
-        Acc acc = Acc{0, 0, 0, 0};
-#pragma unroll
-        for (int kb = 0; kb < 16; ++kb) {
-            if (kb >= kbn) break;
-            acc = Tile::mfma(za[kb], vv[kb], acc);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int col = Tile::drow(r, lane);
-            if (live && col < kc) Bc[row + (int64_t)col * ldb] -= (double)acc[r];
-        }
+    auto run = [&](auto nt) {
+        chunk_minus_vz<Tile, decltype(nt)::value>(V + r0, ldv, B + r0, ldb, Z, r0, ch == 0 ? n : 0, valid, n, kc);
+    };
+    switch ((n + 15) >> 4) {
+        case 1: run(std::integral_constant<int, 1>{}); break;
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        default: run(std::integral_constant<int, 4>{});
     }
 }
 
@@ -872,31 +930,36 @@ __device__ __forceinline__ bool chunk_of(const BMat &M, int64_t g, int64_t &dom,
     return true;
 }
 
+// MIXED: only mixed matrices are listed (every refinement sweep's list): the
+// FP64 form's registers would halve the waves in flight.
+template <bool MIXED>
 __global__ __launch_bounds__(256) void k_apply_p1_b(const BMat *__restrict__ mats, const int *__restrict__ list,
                                                     int sweep) {
     const BMat &M = mats[list[blockIdx.y]];
     int64_t dom, ch;
     if (!chunk_of(M, blockIdx.x, dom, ch)) return;
     if (sweep > 0 && M.status[1]) return;
-    if (M.prec) apply_p1_body<TileF32>(M.V32, M.pa.m, M.pa, M.F, M.pa.m, 1, M.Pc, dom, ch);
+    if (MIXED || M.prec) apply_p1_body<TileF32>(M.V32, M.pa.m, M.pa, M.F, M.pa.m, 1, M.Pc, dom, ch);
     else apply_p1_body<TileF64>(M.V, M.pa.m, M.pa, M.F, M.pa.m, 1, M.Pc, dom, ch);
 }
 
+template <bool QT>
 __global__ __launch_bounds__(256) void k_apply_p2_b(const BMat *__restrict__ mats, const int *__restrict__ list,
-                                                    int trans, int sweep) {
+                                                    int sweep) {
     const BMat &M = mats[list[blockIdx.y]];
     if ((int64_t)blockIdx.x >= M.pa.P) return;
     if (sweep > 0 && M.status[1]) return;
-    apply_p2_body(M.V, M.V32, M.pa.m, M.Tc, M.pa, M.F, M.pa.m, 1, trans, M.Pc, M.Zc, blockIdx.x);
+    apply_p2_body<QT>(M.V, M.V32, M.pa.m, M.Tc, M.pa, M.F, M.pa.m, 1, M.Pc, M.Zc, blockIdx.x);
 }
 
+template <bool MIXED>
 __global__ __launch_bounds__(256) void k_apply_p3_b(const BMat *__restrict__ mats, const int *__restrict__ list,
                                                     int sweep) {
     const BMat &M = mats[list[blockIdx.y]];
     int64_t dom, ch;
     if (!chunk_of(M, blockIdx.x, dom, ch)) return;
     if (sweep > 0 && M.status[1]) return;
-    if (M.prec) apply_p3_body<TileF32>(M.V32, M.pa.m, M.pa, M.F, M.pa.m, 1, M.Zc, dom, ch);
+    if (MIXED || M.prec) apply_p3_body<TileF32>(M.V32, M.pa.m, M.pa, M.F, M.pa.m, 1, M.Zc, dom, ch);
     else apply_p3_body<TileF64>(M.V, M.pa.m, M.pa, M.F, M.pa.m, 1, M.Zc, dom, ch);
 }
 
@@ -904,27 +967,23 @@ hipError_t launch_apply3_b(const BMat *mats, const int *list, int cnt, int64_t m
                            int trans, int sweep, hipStream_t st) {
     if (cnt <= 0 || max_chunks <= 0) return hipSuccess;
     const size_t sh = vtb_lds_bytes<TileF64>(1);   // k = 1
-    hipError_t e = hipFuncSetAttribute((const void *)k_apply_p1_b, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)sh);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_apply_p2_b, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)sizeof(ChainSmem));
+    const auto p1 = sweep > 0 ? k_apply_p1_b<true> : k_apply_p1_b<false>;
+    const auto p3 = sweep > 0 ? k_apply_p3_b<true> : k_apply_p3_b<false>;
+    hipError_t e = hipFuncSetAttribute((const void *)p1, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
     {
         ProfScope ps(trans ? "batch_apply3_p1_qt" : "batch_apply3_p1_q", st);
-        hipLaunchKernelGGL(k_apply_p1_b, dim3((unsigned)max_chunks, (unsigned)cnt), dim3(256), sh, st, mats, list,
-                           sweep);
+        hipLaunchKernelGGL(p1, dim3((unsigned)max_chunks, (unsigned)cnt), dim3(256), sh, st, mats, list, sweep);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     {
         ProfScope ps(trans ? "batch_apply3_p2_qt" : "batch_apply3_p2_q", st);
-        hipLaunchKernelGGL(k_apply_p2_b, dim3((unsigned)max_p, (unsigned)cnt), dim3(256), sizeof(ChainSmem), st,
-                           mats, list, trans, sweep);
+        const auto kern = trans ? k_apply_p2_b<true> : k_apply_p2_b<false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)max_p, (unsigned)cnt), dim3(256), 0, st, mats, list, sweep);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     ProfScope ps(trans ? "batch_apply3_p3_qt" : "batch_apply3_p3_q", st);
-    hipLaunchKernelGGL(k_apply_p3_b, dim3((unsigned)max_chunks, (unsigned)cnt), dim3(256), 0, st, mats, list,
-                       sweep);
+    hipLaunchKernelGGL(p3, dim3((unsigned)max_chunks, (unsigned)cnt), dim3(256), 0, st, mats, list, sweep);
     return hipGetLastError();
 }
 
@@ -936,9 +995,6 @@ static hipError_t launch_apply3(const typename Tile::T *V, const double *V64, co
     const size_t sh = vtb_lds_bytes<Tile>(k);
     hipError_t e = hipFuncSetAttribute((const void *)k_apply_p1<Tile>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_apply_p2, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)sizeof(ChainSmem));
     if (e != hipSuccess) return e;
     const dim3 chunks((unsigned)max_domain_chunks(pa), (unsigned)pa.P);
     {
@@ -948,8 +1004,8 @@ static hipError_t launch_apply3(const typename Tile::T *V, const double *V64, co
     }
     {
         ProfScope ps(trans ? "apply3_p2_qt" : "apply3_p2_q", st);
-        hipLaunchKernelGGL(k_apply_p2, dim3((unsigned)pa.P), dim3(256), sizeof(ChainSmem), st, V64, V32, ldv,
-                           Tc, pa, B, ldb, k, trans, Pc, Zc);
+        const auto kern = trans ? k_apply_p2<true> : k_apply_p2<false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)pa.P), dim3(256), 0, st, V64, V32, ldv, Tc, pa, B, ldb, k, Pc, Zc);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     ProfScope ps(trans ? "apply3_p3_qt" : "apply3_p3_q", st);

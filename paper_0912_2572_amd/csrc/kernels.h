@@ -251,7 +251,7 @@ hipError_t launch_tree_t_b(const BMat *mats, const int *list, int cnt, int64_t m
 hipError_t launch_sign_b(const BMat *mats, const int *list, int cnt, hipStream_t st);
 // Q^T (trans = 1) or Q (trans = 0) on F, leaves, in three chunk-parallel
 // passes (grid.x: max_chunks for passes 1 and 3, max_p for pass 2); sweep > 0
-// skips converged matrices.
+// skips converged matrices and lists mixed ones only.
 hipError_t launch_apply3_b(const BMat *mats, const int *list, int cnt, int64_t max_chunks, int64_t max_p,
                            int trans, int sweep, hipStream_t st);
 // one tree level; step counts from the bottom (trans = 1) or the top (0)

@@ -281,38 +281,41 @@ __device__ __forceinline__ void refine_step(const double *__restrict__ R, int n,
                                             double *__restrict__ X, int64_t ldx, double tol,
                                             int32_t *__restrict__ status, double *__restrict__ hist,
                                             double *__restrict__ gnorm) {
-    __shared__ double g[256];
+    __shared__ double g[256], part[1024];
     const int tid = threadIdx.x, lane = tid & 63;
+    // np entries wide, the workgroup's threads sum parts of the blocks at once
+    const int np = (n + 63) / 64 * 64, parts = (int)blockDim.x / np;
     bool all_ok = true;
     for (int c = 0; c < k; ++c) {
-        // g = -sum_b gpart[b] (every thread), in a fixed order per entry:
-        // even blocks into s0, odd blocks into s1, in block order.  The loads
-        // go out 16 at a time ahead of the adds (the sum waits on memory
-        // latency, not on the adds); the order of the adds is unchanged.
+        // g = -sum_b gpart[b], in a fixed order per entry: part p takes blocks
+        // p, p + parts, ..., alternately into s0 and s1, the parts meet in
+        // order.  The loads go out 16 at a time ahead of the adds (the sum
+        // waits on memory latency, not on the adds).
         __syncthreads();
-        for (int j = tid; j < n; j += blockDim.x) {
+        const int j = tid % np, p0 = tid / np;
+        if (p0 < parts) {
             double s0 = 0.0, s1 = 0.0;
-            if (gpart) {
+            if (gpart && j < n) {
                 const double *__restrict__ p = gpart + j + (int64_t)n * c;
                 const int64_t bs = (int64_t)n * k;
-                int b = 0;
-                for (; b + 15 < nblocks; b += 16) {
+                for (int b = p0; b < nblocks; b += 16 * parts) {
                     double v[16];
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) v[u] = p[(int64_t)(b + u) * bs];
+                    for (int u = 0; u < 16; ++u) v[u] = p[(int64_t)(b + u * parts < nblocks ? b + u * parts : b) * bs];
 #pragma unroll
                     for (int u = 0; u < 16; u += 2) {
-                        s0 += v[u];
-                        s1 += v[u + 1];
+                        s0 += b + u * parts < nblocks ? v[u] : 0.0;
+                        s1 += b + (u + 1) * parts < nblocks ? v[u + 1] : 0.0;
                     }
                 }
-                for (; b + 1 < nblocks; b += 2) {
-                    s0 += p[(int64_t)b * bs];
-                    s1 += p[(int64_t)(b + 1) * bs];
-                }
-                if (b < nblocks) s0 += p[(int64_t)b * bs];
             }
-            g[j] = -(s0 + s1);
+            part[tid] = s0 + s1;
+        }
+        __syncthreads();
+        if (tid < n) {
+            double s = 0.0;
+            for (int p = 0; p < parts; ++p) s += part[p * np + tid];
+            g[tid] = -s;
         }
         __syncthreads();
         if (tid < 64) {   // the solves run on one wave
@@ -364,7 +367,10 @@ __device__ __forceinline__ void refine_step(const double *__restrict__ R, int n,
     }
 }
 
-__global__ __launch_bounds__(256) void k_lsq_refine(const double *__restrict__ R, int n,
+// 512 threads: 1,024 blocks' partials of 128 entries are then summed by 4 parts
+// at once (152 -> 134 us a sweep with the two solves; 1,024 threads left the
+// solves too few registers, 180 us).
+__global__ __launch_bounds__(512) void k_lsq_refine(const double *__restrict__ R, int n,
                                                     double *__restrict__ F, int64_t m, int k,
                                                     const double *__restrict__ gpart, int nblocks,
                                                     double *__restrict__ X, int64_t ldx, double tol,
@@ -520,8 +526,15 @@ __global__ __launch_bounds__(256) void k_refine_b(const BMat *__restrict__ mats,
     const int n = M.pa.n;
     const int64_t m = M.pa.m;
     if (!M.prec) {
+        // 16 loads ahead of the adds
         double s = 0.0;
-        for (int64_t r = n + threadIdx.x; r < m; r += 256) s = fma(M.F[r], M.F[r], s);
+        for (int64_t r = n + threadIdx.x; r < m; r += 16 * 256) {
+            double v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = M.F[r + 256 * u < m ? r + 256 * u : r];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) s = r + 256 * u < m ? fma(v[u], v[u], s) : s;
+        }
         red[threadIdx.x] = s;
         __syncthreads();
         for (int w = 128; w > 0; w >>= 1) {
@@ -678,7 +691,7 @@ hipError_t launch_lsq_refine(const double *R, int n, double *F, int64_t m, int k
                              int nblocks, double *X, int64_t ldx, double tol, int32_t *status,
                              double *hist, double *gnorm, hipStream_t st) {
     ProfScope ps("lsq_refine", st);
-    hipLaunchKernelGGL(k_lsq_refine, dim3(1), dim3(256), 0, st, R, n, F, m, k, gpart, nblocks, X, ldx, tol,
+    hipLaunchKernelGGL(k_lsq_refine, dim3(1), dim3(512), 0, st, R, n, F, m, k, gpart, nblocks, X, ldx, tol,
                        status, hist, gnorm);
     return hipGetLastError();
 }
