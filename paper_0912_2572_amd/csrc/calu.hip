@@ -21,6 +21,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "mfma.h"
+#include "panel_qr.h"
 #include "prof.h"
 
 namespace tsqr {
@@ -212,82 +213,111 @@ void k_calu_trsm(double *__restrict__ A, int64_t lda, int64_t n, int64_t k, int 
         if (i < b) col[i] = y[i];
 }
 
-// A(i, c) -= sum_{kk < K} A(i, k + kk) A(k + kk, c) for i in [r0, m),
-// c in [r0, n), r0 = k + K: 64 x 64 tiles (bi = id mod Tr, bc = id / Tr),
-// four waves in a 2 x 2 grid of 32 x 32 sub-tiles.
-__global__ __launch_bounds__(256) void k_lu_update(double *__restrict__ A, int64_t lda, int64_t m, int64_t n,
-                                                   int64_t k, int K, int64_t Tr) {
-    constexpr int TILE = 64, WT = 2;
-    __shared__ double As[2][16][TILE];
-    __shared__ double Bs[2][16][TILE];
-    const int64_t r0 = k + K;
+// A(i, c) -= sum_{kk < 64} A(i, k + kk) A(k + kk, c) for i in [r0, m),
+// c in [r0, n), r0 = k + 64: 64 x 64 tiles (bi = id mod Tr, bc = id / Tr),
+// four waves in a 2 x 2 grid of 32 x 32 sub-tiles, the product formed
+// transposed (a store covers 16 rows of a column).  A 16-deep chunk of both
+// operands sits in LDS, two depths side by side (a 16-byte read feeds two
+// products), the next chunk's loads in flight; rows and columns past the end
+// repeat the last one and nothing in the loop is conditional; C is read in one
+// batch.  Measured: 4,096 x 4,096's 63 updates 2.63 -> 1.79 ms, against guarded
+// loads with their own addresses and a wait for each entry of C.
+// (Only the last panel is narrower than 64, and nothing follows it.)
+__global__ __launch_bounds__(256, 4) void k_lu_update(double *__restrict__ A, int64_t lda, int64_t m, int64_t n,
+                                                      int64_t k, int64_t Tr) {
+    constexpr int TILE = 64, NCH = kLuPanel / 16;
+    __shared__ double2 As[2][8][TILE], Bs[2][8][TILE];   // [buffer][depths 2 q, 2 q + 1][row or column]
+    const int64_t r0 = k + kLuPanel;
     const int64_t bi = (int64_t)blockIdx.x % Tr, bc = (int64_t)blockIdx.x / Tr;
     const int64_t i0 = r0 + bi * TILE, c0 = r0 + bc * TILE;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int w = wave_index<4>(), lane = threadIdx.x & 63;
     const int wi = w >> 1, wj = w & 1;
 
-    // A operand: row i0 + (tid & 63), depth (tid >> 6) + 4 q; B operand:
-    // depth tid & 15 (16 consecutive rows of U12), column c0 + (tid >> 4) + 16 q
-    const int arow = tid & 63, ak = tid >> 6;
-    const int bk = tid & 15, bcol = tid >> 4;
-    const bool aok = i0 + arow < m;
-    const double *__restrict__ Aa = A + (aok ? i0 + arow : 0) + k * lda;
-    double ra[4], rb[4];
-    auto load = [&](int ch) {
+    // A operand: row i0 + lane, depths 4 w ..; B operand: depths 2 (lane & 7)
+    // .. + 1 (16 consecutive rows of U12 over 8 lanes), columns c0 + 16 w +
+    // lane / 8 and 8 further on
+    const double *Aa = A + (i0 + lane < m ? i0 + lane : m - 1) + (k + 4 * w) * lda;
+    const int bk = lane & 7, bcol = 16 * w + (lane >> 3);
+    const double *Ab[2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int kk = 16 * ch + ak + 4 * q;
-            ra[q] = (aok && kk < K) ? Aa[kk * lda] : 0.0;
-            const int kb = 16 * ch + bk;
-            const int64_t c = c0 + bcol + 16 * q;
-            rb[q] = (kb < K && c < n) ? A[(k + kb) + c * lda] : 0.0;
+    for (int q = 0; q < 2; ++q) {
+        const int64_t c = c0 + bcol + 8 * q;
+        Ab[q] = A + k + 2 * bk + (c < n ? c : n - 1) * lda;
+    }
+    double ra[4], rb[2][2];
+    auto load = [&] {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ra[q] = Aa[q * lda];
+        Aa += 16 * lda;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            rb[q][0] = Ab[q][0];
+            rb[q][1] = Ab[q][1];
+            Ab[q] += 16;
         }
     };
     auto stash = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            As[buf][ak + 4 * q][arow] = ra[q];
-            Bs[buf][bk][bcol + 16 * q] = rb[q];
-        }
+        As[buf][2 * w][lane] = double2{ra[0], ra[1]};
+        As[buf][2 * w + 1][lane] = double2{ra[2], ra[3]};
+        Bs[buf][bk][bcol] = double2{rb[0][0], rb[0][1]};
+        Bs[buf][bk][bcol + 8] = double2{rb[1][0], rb[1][1]};
     };
-    d4 acc[WT][WT];
+    d4 acc[2][2];
 #pragma unroll
-    for (int I = 0; I < WT; ++I)
+    for (int I = 0; I < 2; ++I)
 #pragma unroll
-        for (int J = 0; J < WT; ++J) acc[I][J] = d4_zero();
-    const int nch = (K + 15) / 16;
-    load(0);
+        for (int J = 0; J < 2; ++J) acc[I][J] = d4_zero();
+    load();
     stash(0);
     __syncthreads();
-    const int ri = wi * (TILE / 2) + (lane & 15), rj = wj * (TILE / 2) + (lane & 15);
-    for (int ch = 0; ch < nch; ++ch) {
+    const int ri = 32 * wi + (lane & 15), rj = 32 * wj + (lane & 15), kq = lane >> 4;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
         const int buf = ch & 1;
-        if (ch + 1 < nch) load(ch + 1);
+        if (ch + 1 < NCH) load();
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int kk = 4 * ks + (lane >> 4);
-            double a[WT], bv[WT];
+        for (int ks = 0; ks < 2; ++ks) {
+            double2 a[2], b[2];
 #pragma unroll
-            for (int I = 0; I < WT; ++I) a[I] = As[buf][kk][ri + 16 * I];
+            for (int I = 0; I < 2; ++I) a[I] = As[buf][4 * ks + kq][ri + 16 * I];
 #pragma unroll
-            for (int J = 0; J < WT; ++J) bv[J] = Bs[buf][kk][rj + 16 * J];
+            for (int J = 0; J < 2; ++J) b[J] = Bs[buf][4 * ks + kq][rj + 16 * J];
 #pragma unroll
-            for (int I = 0; I < WT; ++I)
+            for (int I = 0; I < 2; ++I)
 #pragma unroll
-                for (int J = 0; J < WT; ++J) acc[I][J] = mfma_f64(a[I], bv[J], acc[I][J]);
+                for (int J = 0; J < 2; ++J) acc[I][J] = mfma_f64(b[J].x, a[I].x, acc[I][J]);
+#pragma unroll
+            for (int I = 0; I < 2; ++I)
+#pragma unroll
+                for (int J = 0; J < 2; ++J) acc[I][J] = mfma_f64(b[J].y, a[I].y, acc[I][J]);
         }
-        if (ch + 1 < nch) stash(buf ^ 1);
+        if (ch + 1 < NCH) stash(buf ^ 1);
         __syncthreads();
     }
+    d4 c[2][2];
+    auto at = [&](int I, int J, int r, bool &ok) {
+        const int64_t row = i0 + 32 * wi + 16 * I + d_col(lane), col = c0 + 32 * wj + 16 * J + d_row(r, lane);
+        ok = row < m && col < n;
+        return ok ? row + col * lda : r0 + r0 * lda;
+    };
 #pragma unroll
-    for (int I = 0; I < WT; ++I)
+    for (int I = 0; I < 2; ++I)
 #pragma unroll
-        for (int J = 0; J < WT; ++J)
+        for (int J = 0; J < 2; ++J)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t row = i0 + wi * (TILE / 2) + 16 * I + d_row(r, lane);
-                const int64_t col = c0 + wj * (TILE / 2) + 16 * J + d_col(lane);
-                if (row < m && col < n) A[row + col * lda] -= acc[I][J][r];
+                bool ok;
+                c[I][J][r] = A[at(I, J, r, ok)];
+            }
+#pragma unroll
+    for (int I = 0; I < 2; ++I)
+#pragma unroll
+        for (int J = 0; J < 2; ++J)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                bool ok;
+                const int64_t e = at(I, J, r, ok);
+                if (ok) A[e] = c[I][J][r] - acc[I][J][r];
             }
 }
 
@@ -336,7 +366,7 @@ hipError_t launch_calu_panel_rest(double *A, int64_t lda, int64_t m, int64_t n, 
         const int64_t Tr = (m - k - b + 63) / 64, Tc = (n - k - b + 63) / 64;
         if (Tr * Tc > INT32_MAX) return hipErrorInvalidValue;
         ProfScope ps("calu_update", st);
-        hipLaunchKernelGGL(k_lu_update, dim3((unsigned)(Tr * Tc)), dim3(256), 0, st, A, lda, m, n, k, b, Tr);
+        hipLaunchKernelGGL(k_lu_update, dim3((unsigned)(Tr * Tc)), dim3(256), 0, st, A, lda, m, n, k, Tr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
