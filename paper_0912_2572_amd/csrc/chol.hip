@@ -156,27 +156,8 @@ __global__ __launch_bounds__(256) void k_chol_diag(double *__restrict__ A, int64
     chol_diagonal_out(S, A, lda, 0, sb, fail, &flag, dinfo);
 }
 
-// x L11^T = a on 16 columns: u[K] = u[K] / L(K, K), then u[j] -= u[K] L(j, K),
-// row j of -L11 in lane j of every 16-lane row (column K: nl[K]), 1 / L(j, j)
-// in lane j (ri).
-template <int K>
-struct LowerSolve {
-    __device__ __forceinline__ static void run(double (&u)[16], const double (&nl)[16], double ri) {
-        u[K] *= wave_bcast(ri, K);
-        if constexpr (K < 15) {
-            row_terms<K + 1>(u, nl[K], u[K]);
-            LowerSolve<K + 1>::run(u, nl, ri);
-        }
-    }
-};
-
 // Rows s + 64 + 16 blockIdx.x + 0 .. 15 of panel s .. s + 63 against its
-// factored diagonal block, on one wave, right-looking over four 16-column
-// tiles.  A tile waits as a transposed matrix-core accumulator (lane: row
-// lane % 16, columns 4 r + lane / 16); when its turn comes it passes through
-// LDS so that every 16-lane row holds whole rows of it (lane = row, 16 columns
-// in registers), is solved with the entries of its diagonal tile as DPP
-// operands, and updates the tiles after it.  What bounds it: latency -- the
+// factored diagonal block, on one wave (solve_rows16).  What bounds it: latency -- the
 // loads, then 4 x 136 multiply-adds and 24 matrix-core tiles in a chain (about
 // 5 thousand cycles); 16 rows a wave give 8,192 rows two waves per unit.
 // Measured: 9.4 us a panel of 8,192 rows; 16.4 us with 64 rows a wave, all
@@ -207,25 +188,12 @@ void k_chol_solve(double *__restrict__ A, int64_t lda, int64_t n, int64_t s, con
             for (int q = 0; q < 4; ++q) lo[p][t][q] = Ld[16 * t + l16 + (16 * p + 4 * q + l4) * lda];
     }
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) X[4 * q + l4][l16] = c[p][q];
-        __syncthreads();
-        double u[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) u[k] = X[k][l16];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; ++k) nl[p][k] = k < l16 ? -nl[p][k] : 0.0;
-        LowerSolve<0>::run(u, nl[p], 1.0 / dg[p]);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const double x = l4 & 2 ? (l4 & 1 ? u[4 * q + 3] : u[4 * q + 2]) : (l4 & 1 ? u[4 * q + 1] : u[4 * q]);
-            if (r < n) Ar[(16 * p + 4 * q + l4) * lda] = x;
-#pragma unroll
-            for (int t = p + 1; t < 4; ++t) c[t] = mfma_f64(-lo[p][t][q], x, c[t]);
-        }
-    }
+    for (int p = 0; p < 4; ++p) dg[p] = 1.0 / dg[p];
+    solve_rows16(
+        c, nl, lo, X, [&](double v, int p, int K) { return v * wave_bcast(dg[p], K); },
+        [&](int col, double x) {
+            if (r < n) Ar[col * lda] = x;
+        });
 }
 
 // C(i, c) -= sum_{k < 16 nch} A(i, kc + k) A(c, kc + k) for t0 <= c < cend,

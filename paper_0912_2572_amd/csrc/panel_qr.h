@@ -209,6 +209,52 @@ __device__ __forceinline__ void row_terms(double (&u)[16], double g, double t) {
     asm("s_nop 1" : "+v"(g));
     RowTerms<J0>::run(u, g, t);
 }
+// x L^T = a on 16 columns of one row (lane = row, u[j] its columns): x_K =
+// scale(u[K], K), then u[j] -= x_K L(j, K), j > K, with row j of -L in lane j of
+// every 16-lane row (column K: nl[K]).
+template <int K, typename F>
+__device__ __forceinline__ void lower_solve(double (&u)[16], const double (&nl)[16], F scale) {
+    u[K] = scale(u[K], K);
+    if constexpr (K < 15) {
+        row_terms<K + 1>(u, nl[K], u[K]);
+        lower_solve<K + 1>(u, nl, scale);
+    }
+}
+
+// x L^T = a for 16 rows (lane % 16) and 64 columns on one wave, right-looking
+// over four 16-column tiles.  c[t]: tile t as a transposed matrix-core
+// accumulator (column 16 t + 4 q + lane / 16 in register q); nl[p][k]: L(16 p +
+// lane % 16, 16 p + k), used for k < lane % 16; lo[p][t][q]: L(16 t + lane % 16,
+// 16 p + 4 q + lane / 16), t > p.  A tile's turn: through LDS, so that every
+// 16-lane row holds whole rows of it, solved, handed to out(column, x) and
+// applied to the tiles after it.  scale(v, p, K): the division by L's diagonal
+// entry 16 p + K.
+template <typename S, typename F>
+__device__ __forceinline__ void solve_rows16(d4 (&c)[4], double (&nl)[4][16], const double (&lo)[4][4][4],
+                                             double (&X)[16][17], S scale, F out) {
+    const int lane = threadIdx.x & 63, l16 = lane & 15, l4 = lane >> 4;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) X[4 * q + l4][l16] = c[p][q];
+        __syncthreads();
+        double u[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) u[k] = X[k][l16];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) nl[p][k] = k < l16 ? -nl[p][k] : 0.0;
+        lower_solve<0>(u, nl[p], [&](double v, int K) { return scale(v, p, K); });
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double x = l4 & 2 ? (l4 & 1 ? u[4 * q + 3] : u[4 * q + 2]) : (l4 & 1 ? u[4 * q + 1] : u[4 * q]);
+            out(16 * p + 4 * q + l4, x);
+#pragma unroll
+            for (int t = p + 1; t < 4; ++t) c[t] = mfma_f64(-lo[p][t][q], x, c[t]);
+        }
+    }
+}
+
 template <int J, int K>
 struct TColumn {
     __device__ __forceinline__ static void run(const PanelRegs &pr, double g, double &a0, double &a1) {

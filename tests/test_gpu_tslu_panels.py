@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 # rows and row block: domains of several stages with a ragged last stack; of
 # one full stack; of just over b rows; a single stack
 @pytest.mark.parametrize("b", [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64])
-@pytest.mark.parametrize("m,mb", [(2500, 700), (1024, 256), (330, 66), (65, 128)])
+@pytest.mark.parametrize("m,mb", [(2500, 700), (1024, 256), (330, 66), (65, 128), (16384, 4096), (16385, 4096)])
 def test_selection_panel_edges(tl, m, mb, b):  # noqa: F811
     print(f"case tslu m={m} b={b} mb={mb}", flush=True)
     check_tslu(tl, synth.gaussian(m, b, seed=1000 * b + m), tl.opts(row_block=mb, tree=2), 2)
