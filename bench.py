@@ -396,7 +396,7 @@ def sub_records(args):
             "ms": ch["ms_per_step"], "gflops": ch["value"], "info": ch["info"],
             "torch_linalg_cholesky_ms": ch["torch_linalg_cholesky_ms"], "speedup_vs_torch": ch["speedup_vs_torch"],
             "syrk_ms": ch["kernels_ms_per_step"].get("chol_syrk"), "syrk_tflops": ch["syrk_tflops"],
-            "panel_ms": ch["kernels_ms_per_step"].get("chol_panel"),
+            "panel_ms": sum(ch["kernels_ms_per_step"].get(k, 0.0) for k in ("chol_diag", "chol_solve")),
             "sampled_backward_error": ch["sampled_backward_error"], "wall_s": round(t5d - t5c, 1)},
         "calu_4096": {
             "ms": cl["ms_per_step"], "gflops": cl["value"], "info": cl["info"],
@@ -1043,10 +1043,12 @@ def measure_orth(args, steps, warmup, m=1 << 20, b=16, nblocks=16):
     # useful flops: four block products per block (2 m nv b each) and TSQR +
     # thin Q of the m x b block (2 (2 m b^2 - 2 b^3 / 3))
     flops = sum(4 * 2.0 * m * (j * b) * b + 2 * (2.0 * m * b * b - 2.0 * b ** 3 / 3.0) for j in range(nblocks))
-    # algorithmic HBM bytes: V read four times, W read/written by the
-    # projections, the block read by TSQR, V and Q written by TSQR
-    alg = sum(4 * 8.0 * m * j * b + 6 * 8.0 * m * b + 3 * 8.0 * m * b for j in range(nblocks))
-    upd_cnt, upd_ms = kern.get("orth_proj_update", (0, 0.0))
+    # algorithmic HBM bytes: V read three times (four past 128 columns), W
+    # read/written by the projections, the block read by TSQR, V and Q written
+    # by TSQR
+    alg = sum((3 if j * b <= 128 else 4) * 8.0 * m * j * b + 6 * 8.0 * m * b + 3 * 8.0 * m * b
+              for j in range(nblocks))
+    upd_ms = sum(kern.get(k, (0, 0.0))[1] for k in ("orth_proj_update", "orth_proj_both"))
     upd_bytes = sum(2 * (8.0 * m * j * b + 16.0 * m * b) for j in range(1, nblocks))
     line = {
         "metric": "block orthogonalisation (block Gram-Schmidt x2 + TSQR) Gflop/s in a block Krylov loop",
