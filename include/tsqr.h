@@ -108,7 +108,9 @@ typedef struct {
                              /* of a wider matrix is balanced on its own.  */
     double refine_tol;       /* stop when the error left, estimated as
                                 ||dx|| times the sweep-to-sweep contraction
-                                ||dx|| / ||dx_prev||, is <= tol ||x||       */
+                                ||dx|| / ||dx_prev||, is <= tol ||x|| and,
+                                for tol <= 1e-12, the last residual pass
+                                shows it (the bound behind dinfo = -3)      */
     double route_kappa;      /* mixed: the first tsqr_lsq_solve of a factor
                                 estimates kappa_1(R) (tsqr_cond_estimate);
                                 above route_kappa (or not finite) it factors
@@ -501,7 +503,7 @@ TSQR_API size_t tsqr_batch_workspace_bytes(int count, const tsqr_batch_item *ite
    handle.  refine_sweeps: refinement sweeps after the first solve for the
    mixed matrices (each stops early on its own once its estimated remaining
    error (||dx|| times the observed contraction) is <= refine_tol ||x||
-   or it stalls; the sweeps are part of the captured graph, so no host
+   (tsqr_opts.refine_tol) or it stalls; the sweeps are part of the captured graph, so no host
    synchronisation happens inside a run).  Errors: -1 count, -2 items (an
    item out of scope: its index is reported by tsqr_batch_bad_item), -3 tune,
    -5 refine arguments, TSQR_ERR_WORKSPACE, -1000-e. */

@@ -379,8 +379,8 @@ static int lsq_solve_mixed(tsqr_factors_s *f, const double *A, int64_t lda, int6
             TRY(tsqr::launch_lsq_resid(A, lda, m, n, Bg, ldb, Xw, n, Rr, F, kg, gpart, rpart, nb, st));
             int rc = tsqr_apply_qt(f, kg, F, m, st);
             if (rc) return rc;
-            TRY(tsqr::launch_lsq_refine(Rf, n, F, m, kg, gpart, nb, Xw, n, P.opts.refine_tol, status, hist,
-                                        hist + kmax, st));
+            TRY(tsqr::launch_lsq_refine(Rf, n, F, m, kg, gpart, nb, rpart, Xw, n, P.opts.refine_tol, status,
+                                        hist, hist + kmax, st));
             int32_t hs[2] = {0, 0};
             TRY(hipMemcpyAsync(hs, status, sizeof(hs), hipMemcpyDeviceToHost, st));
             TRY(hipStreamSynchronize(st));

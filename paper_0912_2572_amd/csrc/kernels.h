@@ -234,8 +234,8 @@ hipError_t launch_lsq_resid(const double *A, int64_t lda, int64_t m, int n, cons
                             const double *X, int64_t ldx, const double *Rr, double *F, int k,
                             double *gpart, double *rpart, int nblocks, hipStream_t st);
 hipError_t launch_lsq_refine(const double *R, int n, double *F, int64_t m, int k, const double *gpart,
-                             int nblocks, double *X, int64_t ldx, double tol, int32_t *status,
-                             double *hist, double *gnorm, hipStream_t st);
+                             int nblocks, const double *rpart, double *X, int64_t ldx, double tol,
+                             int32_t *status, double *hist, double *gnorm, hipStream_t st);
 hipError_t launch_axpy(double *y, const double *x, int64_t count, hipStream_t st);
 hipError_t launch_status_init(int32_t *status, double *hist, int k, hipStream_t st);
 hipError_t launch_mixed_final(const double *R, int n, int k, const double *Xw, double *X, int64_t ldx,

@@ -16,6 +16,7 @@
 #include "kernels.h"
 #include "plan.h"
 #include "prof.h"
+#include "refine_rule.h"
 
 namespace tsqr {
 
@@ -265,27 +266,57 @@ __global__ __launch_bounds__(256) void k_lsq_resid(const double *__restrict__ A,
     resid_block(A, lda, m, n, B, ldb, X, ldx, Rr, F, k, gpart, rpart, blockIdx.x, gridDim.x, sh);
 }
 
+// Upper bound on the least-squares backward error of x (Sec. 1 of the
+// paper only names least squares; the bound is the normwise one used to
+// judge refinement):  with the last residual pass's s = b - A x,
+// f = b - r - A x and g = -A^T r,
+//     ||A^T s|| <= ||g|| + ||A|| ||f||,
+//     eta = ||A^T s|| / (||A|| (||A|| ||x|| + ||s||)),
+// and ||A||_F = ||R||_F (A = QR, Q orthogonal).
+__device__ __forceinline__ double eta_bound(double gn, double fn, double sn, double xn, double an) {
+    const double den = an * fma(an, xn, sn);
+    return den > 0.0 ? fma(an, fn, gn) / den : 0.0;
+}
+
+// Sum of v over the workgroup, in every thread (red: a double per wave).
+__device__ __forceinline__ double block_sum(double v, double *red) {
+    v = wave_sum(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = 0.0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += red[w];
+    return t;
+}
+
+// ||R||_F of the n x n triangle, by one workgroup (every thread returns it).
+__device__ __forceinline__ double tri_fnorm(const double *__restrict__ R, int n, double *red) {
+    double s = 0.0;
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) {
+        const int r = e % n, c = e / n;
+        if (r <= c) s = fma(R[e], R[e], s);
+    }
+    return sqrt(block_sum(s, red));
+}
+
 // One workgroup: g = -sum_b gpart[b];  R^T h = g;  dx = R^{-1} (d_1 - h)
 // with d_1 = F[0:n] (= (Q^T f)[0:n] on entry);  X += dx;  F[0:n] = h.
 // status[0] = sweeps done, status[1] = 1 when converged or stalled,
 // hist[c] = ||dx_c|| / ||x_c|| of the last sweep and, if gnorm is set,
-// gnorm[c] = ||g_c||.  A sweep counts as final when every column either
-// converged or stalled (its correction shrank by less than 10 %).  A column
-// has converged when the error left after this sweep's correction,
-// estimated as rho ||dx|| with rho = ||dx|| / ||dx_prev|| the observed
-// contraction of the iteration (at most 1), is below tol ||x|| -- so a
-// sweep whose correction is already far below the tolerance is not needed
-// just to confirm it.
+// gnorm[c] = ||g_c||.  A sweep counts as final when refine_done holds for
+// every column; rpart: the residual pass' partial norms (nullptr: none yet).
 __device__ __forceinline__ void refine_step(const double *__restrict__ R, int n, double *__restrict__ F,
                                             int64_t m, int k, const double *__restrict__ gpart, int nblocks,
-                                            double *__restrict__ X, int64_t ldx, double tol,
-                                            int32_t *__restrict__ status, double *__restrict__ hist,
-                                            double *__restrict__ gnorm) {
-    __shared__ double g[256], part[1024];
+                                            const double *__restrict__ rpart, double *__restrict__ X,
+                                            int64_t ldx, double tol, int32_t *__restrict__ status,
+                                            double *__restrict__ hist, double *__restrict__ gnorm) {
+    __shared__ double g[256], part[1024], red[8], norms[2];   // norms: ||x||, ||g|| of the column
+    __shared__ RefineState state;
     const int tid = threadIdx.x, lane = tid & 63;
     // np entries wide, the workgroup's threads sum parts of the blocks at once
     const int np = (n + 63) / 64 * 64, parts = (int)blockDim.x / np;
     bool all_ok = true;
+    double an = -1.0;   // ||R||_F, once a column asks for it
     for (int c = 0; c < k; ++c) {
         // g = -sum_b gpart[b], in a fixed order per entry: part p takes blocks
         // p, p + parts, ..., alternately into s0 and s1, the parts meet in
@@ -329,8 +360,8 @@ __device__ __forceinline__ void refine_step(const double *__restrict__ R, int n,
                 double gg = 0.0;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) gg = fma(h[q], h[q], gg);
-                gg = wave_sum(gg);
-                if (lane == 0) gnorm[c] = sqrt(gg);
+                gg = sqrt(wave_sum(gg));
+                if (lane == 0) gnorm[c] = norms[1] = gg;
             }
             wave_fwdsub_t(R, n, h);                       // R^T h = g
 #pragma unroll
@@ -353,13 +384,27 @@ __device__ __forceinline__ void refine_step(const double *__restrict__ R, int n,
             }
             a = wave_sum(a);
             b = wave_sum(b);
-            const double rel = sqrt(a) / fmax(sqrt(b), 1e-300);
-            const double prev = hist[c];
-            const double rho = (status[0] >= 1 && prev > 0.0) ? fmin(rel / prev, 1.0) : 1.0;
-            const bool done = (rho * rel <= tol) || (status[0] >= 1 && rel > 0.9 * prev) || !(rel == rel);
-            all_ok = all_ok && done;
-            if (lane == 0) hist[c] = rel;
+            const double xn = sqrt(b), rel = sqrt(a) / fmax(xn, 1e-300);
+            if (lane == 0) {
+                norms[0] = xn;
+                state = refine_state(rel, hist[c], status[0], tol);
+                hist[c] = rel;
+            }
         }
+        __syncthreads();
+        double eta = 0.0;
+        if (state == kRefineConverged && tol <= kEtaMax && rpart && gnorm) {
+            if (an < 0.0) an = tri_fnorm(R, n, red);
+            double sn = 0.0, fn = 0.0;
+            for (int b = tid; b < nblocks; b += blockDim.x) {
+                sn += rpart[(int64_t)b * 2 * k + c];
+                fn += rpart[(int64_t)b * 2 * k + k + c];
+            }
+            sn = sqrt(block_sum(sn, red));
+            fn = sqrt(block_sum(fn, red));
+            eta = eta_bound(norms[1], fn, sn, norms[0], an);
+        }
+        all_ok = all_ok && refine_done(state, tol, rpart != nullptr, eta);
     }
     if (tid == 0) {
         status[0] += 1;
@@ -373,10 +418,10 @@ __device__ __forceinline__ void refine_step(const double *__restrict__ R, int n,
 __global__ __launch_bounds__(512) void k_lsq_refine(const double *__restrict__ R, int n,
                                                     double *__restrict__ F, int64_t m, int k,
                                                     const double *__restrict__ gpart, int nblocks,
-                                                    double *__restrict__ X, int64_t ldx, double tol,
-                                                    int32_t *__restrict__ status,
+                                                    const double *__restrict__ rpart, double *__restrict__ X,
+                                                    int64_t ldx, double tol, int32_t *__restrict__ status,
                                                     double *__restrict__ hist, double *__restrict__ gnorm) {
-    refine_step(R, n, F, m, k, gpart, nblocks, X, ldx, tol, status, hist, gnorm);
+    refine_step(R, n, F, m, k, gpart, nblocks, rpart, X, ldx, tol, status, hist, gnorm);
 }
 
 __global__ void k_axpy(double *__restrict__ y, const double *__restrict__ x, int64_t count) {
@@ -391,36 +436,6 @@ __global__ void k_status_init(int32_t *status, double *hist, int k) {
         status[1] = 0;
     }
     if ((int)threadIdx.x < k) hist[threadIdx.x] = 1.0;
-}
-
-// Upper bound on the least-squares backward error of x (Sec. 1 of the
-// paper only names least squares; the bound is the normwise one used to
-// judge refinement):  with the last residual pass's s = b - A x,
-// f = b - r - A x and g = -A^T r,
-//     ||A^T s|| <= ||g|| + ||A|| ||f||,
-//     eta = ||A^T s|| / (||A|| (||A|| ||x|| + ||s||)),
-// and ||A||_F = ||R||_F (A = QR, Q orthogonal).
-__device__ __forceinline__ double eta_bound(double gn, double fn, double sn, double xn, double an) {
-    const double den = an * fma(an, xn, sn);
-    return den > 0.0 ? fma(an, fn, gn) / den : 0.0;
-}
-
-constexpr double kEtaMax = 1e-12;   // a refined x above this bound is flagged (dinfo = -3)
-
-// ||R||_F of the n x n triangle, by one workgroup (every thread returns it).
-__device__ __forceinline__ double tri_fnorm(const double *__restrict__ R, int n, double *red) {
-    double s = 0.0;
-    for (int e = threadIdx.x; e < n * n; e += blockDim.x) {
-        const int r = e % n, c = e / n;
-        if (r <= c) s = fma(R[e], R[e], s);
-    }
-    s = wave_sum(s);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    double t = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += red[w];
-    return sqrt(t);
 }
 
 // Last step of a refined solve: info from the diagonal of R (LAPACK dtrtrs
@@ -544,8 +559,8 @@ __global__ __launch_bounds__(256) void k_refine_b(const BMat *__restrict__ mats,
         if (threadIdx.x == 0) M.hist[1] = sqrt(red[0]);
         __syncthreads();
     }
-    refine_step(M.R, n, M.F, m, 1, sweep > 0 ? M.gpart : nullptr, M.nb, M.Xw, n, tol, M.status, M.hist,
-                M.prec ? M.hist + 2 : nullptr);
+    refine_step(M.R, n, M.F, m, 1, sweep > 0 ? M.gpart : nullptr, M.nb, sweep > 0 ? M.rpart : nullptr, M.Xw, n, tol,
+                M.status, M.hist, M.prec ? M.hist + 2 : nullptr);
     if (!M.prec && threadIdx.x == 0) M.status[1] = 1;
 }
 
@@ -688,11 +703,11 @@ hipError_t launch_lsq_resid(const double *A, int64_t lda, int64_t m, int n, cons
 }
 
 hipError_t launch_lsq_refine(const double *R, int n, double *F, int64_t m, int k, const double *gpart,
-                             int nblocks, double *X, int64_t ldx, double tol, int32_t *status,
-                             double *hist, double *gnorm, hipStream_t st) {
+                             int nblocks, const double *rpart, double *X, int64_t ldx, double tol,
+                             int32_t *status, double *hist, double *gnorm, hipStream_t st) {
     ProfScope ps("lsq_refine", st);
-    hipLaunchKernelGGL(k_lsq_refine, dim3(1), dim3(512), 0, st, R, n, F, m, k, gpart, nblocks, X, ldx, tol,
-                       status, hist, gnorm);
+    hipLaunchKernelGGL(k_lsq_refine, dim3(1), dim3(512), 0, st, R, n, F, m, k, gpart, nblocks, rpart, X,
+                       ldx, tol, status, hist, gnorm);
     return hipGetLastError();
 }
 
