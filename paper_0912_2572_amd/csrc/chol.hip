@@ -28,7 +28,9 @@
 // the caches by every tile.
 //
 // A failed pivot (<= 0 or NaN) writes j + 1 to the info word; every later
-// kernel reads the word first and returns at once.
+// kernel reads the word first and returns at once.  An update whose own tile
+// (0, 0) fails is not later: its other tiles may read the word before or after
+// it is written, wave by wave, and finish the update either way.
 #include "common.h"
 #include "kernels.h"
 #include "mfma.h"
@@ -212,7 +214,10 @@ void k_chol_solve(double *__restrict__ A, int64_t lda, int64_t n, int64_t s, con
 __global__ __launch_bounds__(256, 4) void k_chol_update(double *__restrict__ A, int64_t lda, int64_t n, int64_t t0,
                                                         int64_t cend, int64_t kc, int nch, int64_t Tr, int64_t Tc,
                                                         int32_t *__restrict__ dinfo) {
-    if (*(const volatile int32_t *)dinfo != 0) return;
+    // a pivot before column t0 failed (tile (0, 0) of this launch writes t0 + 1
+    // or more, which must not part a workgroup's waves)
+    const int32_t failed = *(const volatile int32_t *)dinfo;
+    if (failed != 0 && failed <= t0) return;
     __shared__ __attribute__((aligned(16))) double smem[kPanel * kDiagLd];   // operands, then the diagonal block
     __shared__ int flag;
     double2(*As)[8][kPanel] = reinterpret_cast<double2(*)[8][kPanel]>(smem);   // [buffer][columns 2 q, 2 q + 1][row]
