@@ -322,29 +322,36 @@ void k_tslu_tree(const double *__restrict__ A, int64_t lda, PanelArgs pa, TreeAr
 
 // Step Q of the no-pivot LU of panel p, lane i holding row i's panel entries:
 // rows below row 16 p + Q divide by the pivot and update their entries past
-// Q, the pivot row broadcast by lane reads.  A zero pivot eliminates nothing
-// and sets info.
+// Q, the pivot row broadcast by lane reads; the other rows are left alone (a
+// multiplier of zero would turn their entries into NaN under an infinity of
+// the pivot row).  A zero pivot eliminates nothing, sets info and bit Q of
+// `zeros`.
 template <int Q>
 struct NoPivotStep {
-    __device__ __forceinline__ static void run(double (&m)[16], int i, int p, int nq, int &info) {
+    __device__ __forceinline__ static void run(double (&m)[16], int i, int p, int nq, int &info, uint32_t &zeros) {
         if (Q < nq) {
             const int k = 16 * p + Q;
-            const double piv = wave_bcast(m[Q], k);
-            const bool zero = piv == 0.0;
-            if (zero && !info) info = k + 1;
-            const bool below = i > k && !zero;
-            const double l = below ? m[Q] / piv : 0.0;
-            if (below) m[Q] = l;
+            double row[16];
 #pragma unroll
-            for (int j = Q + 1; j < 16; ++j) m[j] = fma(-l, wave_bcast(m[j], k), m[j]);
+            for (int j = Q; j < 16; ++j) row[j] = wave_bcast(m[j], k);
+            if (row[Q] == 0.0) {
+                if (!info) info = k + 1;
+                zeros |= 1u << Q;
+            } else if (i > k) {
+                m[Q] /= row[Q];
+#pragma unroll
+                for (int j = Q + 1; j < 16; ++j) m[j] = fma(-m[Q], row[j], m[j]);
+            }
         }
-        if constexpr (Q + 1 < 16) NoPivotStep<Q + 1>::run(m, i, p, nq, info);
+        if constexpr (Q + 1 < 16) NoPivotStep<Q + 1>::run(m, i, p, nq, info, zeros);
     }
 };
 
 // U and the unit lower L11 of A[ipiv, :] by elimination without pivoting, in
 // 16-column panels as in select_stack: the steps on one wave (lane i owns row
-// i), the updates on four.  info: the first zero U_jj (1-based), else 0.
+// i), the updates on four.  info: the first zero U_jj (1-based), else 0.  What
+// stands below a zero U_jj goes to L11 as it is; in S zeros take its place, so
+// that the later columns' updates skip it as the steps do.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void k_tslu_u(const double *__restrict__ A, int64_t lda, int b, const int32_t *__restrict__ cand,
               int64_t *__restrict__ ipiv, double *__restrict__ U, int64_t ldu, double *__restrict__ L11,
@@ -372,9 +379,14 @@ void k_tslu_u(const double *__restrict__ A, int64_t lda, int b, const int32_t *_
             double m[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) m[j] = row[16 * p + j];
-            NoPivotStep<0>::run(m, i, p, b - 16 * p, info);
+            uint32_t zeros = 0;
+            NoPivotStep<0>::run(m, i, p, b - 16 * p, info, zeros);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) row[16 * p + j] = m[j];
+            for (int j = 0; j < 16; ++j) {
+                const int k = 16 * p + j;
+                if (i < b && k < b) L11[i + (int64_t)k * 64] = (k < i) ? m[j] : (k == i ? 1.0 : 0.0);
+                row[k] = (k < i && (zeros >> j & 1u)) ? 0.0 : m[j];
+            }
         }
         __syncthreads();
         if (p + 1 == np) break;
@@ -402,7 +414,6 @@ void k_tslu_u(const double *__restrict__ A, int64_t lda, int b, const int32_t *_
             if (k < b) {
                 const double v = row[k];
                 U[i + (int64_t)k * ldu] = (i <= k) ? v : 0.0;
-                L11[i + (int64_t)k * 64] = (k < i) ? v : (k == i ? 1.0 : 0.0);
             }
         }
     }
