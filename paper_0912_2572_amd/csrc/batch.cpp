@@ -124,7 +124,6 @@ struct tsqr_batch_s {
     int *dlists = nullptr;
     int sweeps = 0;
     double tol = 1e-14;
-    int launches = 0;
     hipGraphExec_t exec = nullptr;
 };
 
@@ -158,34 +157,23 @@ void fill_group(Group &g, const std::vector<int> &idx, const tsqr_batch_s &B, in
         if (e_ != hipSuccess) return -1000 - (int)e_;    \
     } while (0)
 
-int enqueue(tsqr_batch_s *B, hipStream_t st, int *launches) {
-    int nl = 0;
+int enqueue(tsqr_batch_s *B, hipStream_t st) {
     const BMat *D = B->dmats;
     auto L = [&](const Group &g) { return B->dlists + g.list_off; };
+    for (const Group &g : B->cls) TRYB(tsqr::launch_leaf_b(D, L(g), g.cnt, g.maxP, g.ns, st));
     for (const Group &g : B->cls) {
-        TRYB(tsqr::launch_leaf_b(D, L(g), g.cnt, g.maxP, g.ns, st));
-        ++nl;
-    }
-    for (const Group &g : B->cls) {
-        for (int lv = 0; lv < g.maxLev; ++lv) {
+        for (int lv = 0; lv < g.maxLev; ++lv)
             TRYB(tsqr::launch_tree_b(D, L(g), g.cnt, g.up[lv], g.ns, lv, st));
-            ++nl;
-        }
         TRYB(tsqr::launch_tree_t_b(D, L(g), g.cnt, g.maxP, g.ns, st));
-        ++nl;
     }
     const Group &A = B->all;
     TRYB(tsqr::launch_sign_b(D, L(A), A.cnt, st));
     TRYB(tsqr::launch_lsq_init_b(D, L(A), A.cnt, (A.maxM + 2047) / 2048, st));
     TRYB(tsqr::launch_apply3_b(D, L(A), A.cnt, A.maxChunks, A.maxP, 1, 0, st));
-    nl += 5;
-    for (int s = 0; s < A.maxLev; ++s) {
+    for (int s = 0; s < A.maxLev; ++s)
         TRYB(tsqr::launch_tree_apply_b(D, L(A), A.cnt, A.up[s], 1, s, 0, st));
-        ++nl;
-    }
     TRYB(tsqr::launch_scale_b(D, L(A), A.cnt, 0, st));
     TRYB(tsqr::launch_refine_b(D, L(A), A.cnt, 0, B->tol, st));
-    nl += 2;
     const Group &X = B->mixed;
     if (X.cnt > 0)
         for (int sw = 1; sw <= B->sweeps; ++sw) {
@@ -202,12 +190,19 @@ int enqueue(tsqr_batch_s *B, hipStream_t st, int *launches) {
                 TRYB(tsqr::launch_tree_apply_b(D, L(X), X.cnt, X.up[s], 1, s, sw, st));
             TRYB(tsqr::launch_scale_b(D, L(X), X.cnt, sw, st));
             TRYB(tsqr::launch_refine_b(D, L(X), X.cnt, sw, B->tol, st));
-            nl += 12 + 2 * X.maxLev;
         }
     TRYB(tsqr::launch_final_b(D, L(A), A.cnt, st));
-    ++nl;
-    if (launches) *launches = nl;
     return 0;
+}
+
+// Launches of one enqueue: fixed by the plan.
+int launch_count(const tsqr_batch_s &B) {
+    int nl = 0;
+    for (const Group &g : B.cls) nl += 1 + g.maxLev + (tsqr::tree_t_needed(g.maxP, g.ns) ? 1 : 0);
+    // signs, right-hand sides, Q^T b in three passes and by levels, scaling, solve
+    nl += 7 + B.all.maxLev;
+    if (B.mixed.cnt > 0) nl += B.sweeps * (11 + 2 * B.mixed.maxLev);
+    return nl + 1;
 }
 
 size_t workspace_for(int count, const tsqr_batch_item *items, const tsqr_tune_entry *tune, int ntune) {
@@ -406,13 +401,13 @@ TSQR_API int tsqr_batch_create(int count, const tsqr_batch_item *items, const ts
 TSQR_API int tsqr_batch_run(tsqr_batch B, int use_graph, void *stream) {
     if (!B) return -1;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (!use_graph) return enqueue(B, st, &B->launches);
+    if (!use_graph) return enqueue(B, st);
     if (!st) return -3;
     if (!B->exec) {
         hipGraph_t g = nullptr;
         TRYB(hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed));
         tsqr::prof_suspend(true);
-        int rc = enqueue(B, st, &B->launches);
+        int rc = enqueue(B, st);
         tsqr::prof_suspend(false);
         hipError_t e = hipStreamEndCapture(st, &g);
         if (rc) {
@@ -442,15 +437,7 @@ TSQR_API int tsqr_batch_plan(tsqr_batch B, int i, int64_t *row_block, int32_t *t
 
 TSQR_API int tsqr_batch_launches(tsqr_batch B) {
     if (!B) return -1;
-    if (B->launches == 0) {
-        // count without launching: the sequence is fixed by the plan
-        int nl = (int)B->cls.size();
-        for (const Group &g : B->cls) nl += g.maxLev;
-        nl += 7 + B->all.maxLev + 1;
-        if (B->mixed.cnt > 0) nl += B->sweeps * (12 + 2 * B->mixed.maxLev);
-        return nl;
-    }
-    return B->launches;
+    return launch_count(*B);
 }
 
 TSQR_API int tsqr_batch_free(tsqr_batch B) {

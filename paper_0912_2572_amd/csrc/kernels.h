@@ -138,6 +138,8 @@ hipError_t launch_tree_level(double *Rdom, double *Tnode, const PanelArgs &pa, c
 // T of every tree node (nodes 1 .. P - 1) from its reflector block and the
 // panels' T the levels stored; launched once after the last level when Q is
 // kept.
+// One panel of 16 columns needs no launch: T is its diagonal block.
+inline bool tree_t_needed(int64_t P, int ns) { return P > 1 && ns > 1; }
 hipError_t launch_tree_t(const double *Rdom, double *Tnode, const PanelArgs &pa, hipStream_t st);
 // The same leaf with the reflectors stored in FP32 (mixed precision).
 hipError_t launch_leaf32(const double *A, int64_t lda, float *V, int64_t ldv, double *Tc, double *Rdom,

@@ -377,7 +377,7 @@ hipError_t launch_tree_b(const BMat *mats, const int *list, int cnt, int64_t gx,
 }
 
 hipError_t launch_tree_t_b(const BMat *mats, const int *list, int cnt, int64_t maxP, int ns, hipStream_t st) {
-    if (cnt <= 0 || maxP <= 1 || ns == 1) return hipSuccess;   // one panel: T is its diagonal block
+    if (cnt <= 0 || !tree_t_needed(maxP, ns)) return hipSuccess;
     const size_t sh = sizeof(NodeTSmem);
     hipError_t e = hipFuncSetAttribute((const void *)k_tree_t_b, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
@@ -415,7 +415,7 @@ hipError_t launch_tree_level(double *Rdom, double *Tnode, const PanelArgs &pa, c
 }
 
 hipError_t launch_tree_t(const double *Rdom, double *Tnode, const PanelArgs &pa, hipStream_t st) {
-    if (pa.P <= 1 || pa.ns == 1) return hipSuccess;   // one panel: T is its diagonal block
+    if (!tree_t_needed(pa.P, pa.ns)) return hipSuccess;
     const size_t sh = sizeof(NodeTSmem);
     hipError_t e = hipFuncSetAttribute((const void *)k_tree_t, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
