@@ -147,11 +147,12 @@ __device__ __forceinline__ void settle(d4 &c) {
 // if sig2 == 0 (H = I, R's entry stays alpha).  1 / |beta| is v_rsq_f64 and
 // one third-order step, 1 / d v_rcp_f64 of the unrefined d and one
 // third-order step on the refined one, so the two short chains overlap.
-// kTiny keeps x > 0 without a branch (it is below the rounding of any x of
-// the supported magnitudes, 2^-400 .. 2^400).
+// kTiny keeps x > 0 without a branch: the smallest denormal, at most one unit in
+// the last place of any normal x (norms from 2^-511 on, where ||x2||^2 leaves the
+// normal range; with x = kTiny every product below is finite).
 __device__ __forceinline__ void panel_scalars(double alpha, double sig2, double &beta, double &tau, double &s,
                                               double &g, double &d) {
-    constexpr double kTiny = 0x1p-1000;
+    constexpr double kTiny = 0x1p-1074;
     const double x = fma(alpha, alpha, sig2) + kTiny;
     const double sgn = (alpha < 0.0) ? -1.0 : 1.0;
     const double r0 = __builtin_amdgcn_rsq(x);
