@@ -324,26 +324,24 @@ void k_tslu_tree(const double *__restrict__ A, int64_t lda, PanelArgs pa, TreeAr
 // rows below row 16 p + Q divide by the pivot and update their entries past
 // Q, the pivot row broadcast by lane reads; the other rows are left alone (a
 // multiplier of zero would turn their entries into NaN under an infinity of
-// the pivot row).  A zero pivot eliminates nothing, sets info and bit Q of
-// `zeros`.
+// the pivot row).  A zero pivot eliminates nothing and sets bit Q of `zeros`.
 template <int Q>
 struct NoPivotStep {
-    __device__ __forceinline__ static void run(double (&m)[16], int i, int p, int nq, int &info, uint32_t &zeros) {
+    __device__ __forceinline__ static void run(double (&m)[16], int i, int p, int nq, uint32_t &zeros) {
         if (Q < nq) {
             const int k = 16 * p + Q;
             double row[16];
 #pragma unroll
             for (int j = Q; j < 16; ++j) row[j] = wave_bcast(m[j], k);
-            if (row[Q] == 0.0) {
-                if (!info) info = k + 1;
-                zeros |= 1u << Q;
-            } else if (i > k) {
+            const bool zero = row[Q] == 0.0;
+            zeros |= zero ? 1u << Q : 0u;
+            if (i > k && !zero) {
                 m[Q] /= row[Q];
 #pragma unroll
                 for (int j = Q + 1; j < 16; ++j) m[j] = fma(-m[Q], row[j], m[j]);
             }
         }
-        if constexpr (Q + 1 < 16) NoPivotStep<Q + 1>::run(m, i, p, nq, info, zeros);
+        if constexpr (Q + 1 < 16) NoPivotStep<Q + 1>::run(m, i, p, nq, zeros);
     }
 };
 
@@ -358,6 +356,7 @@ void k_tslu_u(const double *__restrict__ A, int64_t lda, int b, const int32_t *_
               int32_t *__restrict__ dinfo) {
     __shared__ double S[64 * kSelLd];
     __shared__ double Up[16 * kSelLd];
+    __shared__ uint32_t skip[4];   // columns whose pivot is zero, a word per panel
     const int t = threadIdx.x, w = wave_index<4>(), i = t & 63, cg = i & 15;
     const int32_t gi = (i < b) ? cand[i] : 0;
     if (t < b) ipiv[t] = gi;
@@ -380,13 +379,21 @@ void k_tslu_u(const double *__restrict__ A, int64_t lda, int b, const int32_t *_
 #pragma unroll
             for (int j = 0; j < 16; ++j) m[j] = row[16 * p + j];
             uint32_t zeros = 0;
-            NoPivotStep<0>::run(m, i, p, b - 16 * p, info, zeros);
+            NoPivotStep<0>::run(m, i, p, b - 16 * p, zeros);
+            if (zeros) {
+                if (!info) info = 16 * p + __builtin_ctz(zeros) + 1;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int k = 16 * p + j;
-                if (i < b && k < b) L11[i + (int64_t)k * 64] = (k < i) ? m[j] : (k == i ? 1.0 : 0.0);
-                row[k] = (k < i && (zeros >> j & 1u)) ? 0.0 : m[j];
+                for (int j = 0; j < 16; ++j) {
+                    const int k = 16 * p + j;
+                    if (k < i && (zeros >> j & 1u)) {
+                        if (i < b) L11[i + (int64_t)k * 64] = m[j];
+                        m[j] = 0.0;
+                    }
+                }
             }
+            if (i == 0) skip[p] = zeros;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) row[16 * p + j] = m[j];
         }
         __syncthreads();
         if (p + 1 == np) break;
@@ -414,6 +421,8 @@ void k_tslu_u(const double *__restrict__ A, int64_t lda, int b, const int32_t *_
             if (k < b) {
                 const double v = row[k];
                 U[i + (int64_t)k * ldu] = (i <= k) ? v : 0.0;
+                if (!(k < i && (skip[k >> 4] >> (k & 15) & 1u)))
+                    L11[i + (int64_t)k * 64] = (k < i) ? v : (k == i ? 1.0 : 0.0);
             }
         }
     }
