@@ -42,7 +42,9 @@ constexpr int KBM = 16;   // most columns of B of the three-pass form
 //       summing reflectors 16 w .. 16 w + 15 and adding its rows of Yb (in
 //       registers for the whole chain);
 //   Z:  op(T) W, the same rows per wave;
-//   B:  B - V Z in tiles whose accumulators are B's, stored by columns again.
+//   B:  B - V Z, the product summed by itself (one rounding at B's size; summed
+//       into B it is one per four columns of V, and ||B - Q Q^T B|| a tenth to a
+//       fifth larger), stored by columns again.
 // What bounds it: per chunk of 256 rows, n = 64 and 32 columns, 16.4 thousand
 // cycles of FP64 tiles on each of a compute unit's four waves, of about 30
 // thousand (the rest are the LDS passes and the seven barriers of W and Z),
@@ -362,10 +364,7 @@ __device__ __forceinline__ void leaf_apply_chains(LeafApplySmem<Tile, NT, NB> &s
             for (int rt = 0; rt < RT; ++rt) {
                 Acc c[NB];
 #pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    if constexpr (sizeof(T) == 8) c[j] = Acc{b[rt][j][0], b[rt][j][1], b[rt][j][2], b[rt][j][3]};
-                    else c[j] = Acc{0, 0, 0, 0};
-                }
+                for (int j = 0; j < NB; ++j) c[j] = Acc{0, 0, 0, 0};
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -379,8 +378,9 @@ __device__ __forceinline__ void leaf_apply_chains(LeafApplySmem<Tile, NT, NB> &s
                 for (int j = 0; j < NB; ++j)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        if constexpr (sizeof(T) == 8) b[rt][j][r] = c[j][r];
-                        else b[rt][j][r] += (double)c[j][r];
+                        b[rt][j][r] += (double)c[j][r];
+                        // now, not behind the next branch with every product kept for it
+                        asm volatile("" : "+v"(b[rt][j][r]));
                     }
                 __builtin_amdgcn_sched_barrier(0);
             }
