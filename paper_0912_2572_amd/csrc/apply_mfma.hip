@@ -72,10 +72,11 @@ __device__ __forceinline__ int row_place(int r, int c) {
     else return r ^ (4 * (((c & 3) << 2) | ((c >> 2) & 3)));
 }
 
-template <typename Tile, int NT, int NB>
+// LOW: no domain has more than half a chunk's rows.
+template <typename Tile, int NT, int NB, bool LOW>
 struct LeafApplySmem {
     using T = typename Tile::T;
-    static constexpr int RT = NT == 1 ? 8 : 4;   // 16-row tiles of a wave (chunk_rows)
+    static constexpr int RT = NT == 1 && !LOW ? 8 : 4;   // 16-row tiles of a wave (chunk_rows)
     T V[4][16 * NT][16 * RT];                    // [wave][reflector][row_place]
     // in turn: per wave 16 columns of B; the partials of W that cross waves,
     // W, Z; Yb's exchange
@@ -83,7 +84,7 @@ struct LeafApplySmem {
     static_assert(sizeof(x) >= 3 * NT * 64 * sizeof(typename Tile::Acc) &&
                       sizeof(x) >= 16 * NT * 16 * NB * sizeof(double), "every use fits");
 };
-static_assert(sizeof(LeafApplySmem<TileF64, 4, 2>) <= 160 * 1024, "fits a CU's LDS");
+static_assert(sizeof(LeafApplySmem<TileF64, 4, 2, false>) <= 160 * 1024, "fits a CU's LDS");
 
 // The work of one chain: domain `dom`, columns c0 .. c0 + kc - 1, in groups of
 // 8 domains x ncb column blocks, the column blocks of one domain 8 items
@@ -108,16 +109,18 @@ __device__ __forceinline__ bool apply_item(const PanelArgs &pa, int64_t k, int n
     return true;
 }
 
-template <typename Tile, int NT, int NB, bool QT>
-__device__ __forceinline__ void leaf_apply_chains(LeafApplySmem<Tile, NT, NB> &sm,
+template <typename Tile, int NT, int NB, bool LOW, bool QT>
+__device__ __forceinline__ void leaf_apply_chains(LeafApplySmem<Tile, NT, NB, LOW> &sm,
                                                   const typename Tile::T *__restrict__ Vp, int64_t ldv,
                                                   const double *__restrict__ Tc, const PanelArgs &pa,
                                                   const double *Bsrcp, int64_t ldbs, double *Bp, int64_t ldb,
                                                   int64_t k, int ncb) {
     using T = typename Tile::T;
     using Acc = typename Tile::Acc;
-    using Smem = LeafApplySmem<Tile, NT, NB>;
-    constexpr int RT = Smem::RT, H = RT / 4;   // H rows per lane: lane, lane + 64
+    constexpr int RT = LeafApplySmem<Tile, NT, NB, LOW>::RT, H = RT / 4;   // H rows per lane: lane, lane + 64
+    // Low domains' rows are one or two waves', and one chain of sums over 64 of
+    // them loses more than four over 16: the tiles' sums meet by themselves
+    constexpr bool kTileSums = LOW;
     const int w = wave_index<4>();
     int lane = threadIdx.x & 63;
     const int n = pa.n;
@@ -280,14 +283,23 @@ __device__ __forceinline__ void leaf_apply_chains(LeafApplySmem<Tile, NT, NB> &s
                         for (int i = 0; i < kPer; ++i) a[t][h + i] = p[i];
                     }
                 }
+                Acc part[NT][NB];
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) part[t][j] = kTileSums ? Acc{0, 0, 0, 0} : acc[t][j];
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
                     for (int j = 0; j < NB; ++j) {
                         const T x = T(b[rt][j][r]);
 #pragma unroll
-                        for (int t = 0; t < NT; ++t) acc[t][j] = Tile::mfma(a[t][r], x, acc[t][j]);
+                        for (int t = 0; t < NT; ++t) part[t][j] = Tile::mfma(a[t][r], x, part[t][j]);
                     }
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) acc[t][j] = kTileSums ? acc[t][j] + part[t][j] : part[t][j];
                 __builtin_amdgcn_sched_barrier(0);
             }
             // the partials meet: W's rows 16 w .. on wave w
@@ -443,22 +455,22 @@ __device__ __forceinline__ void leaf_apply_chains(LeafApplySmem<Tile, NT, NB> &s
     }
 }
 
-template <typename Tile, int NT, int NB, bool QT>
+template <typename Tile, int NT, int NB, bool LOW, bool QT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
 void k_leaf_apply_m(const typename Tile::T *__restrict__ V, int64_t ldv, const double *__restrict__ Tc,
                     PanelArgs pa, const double *Bsrc, int64_t ldbs, double *B, int64_t ldb, int64_t k, int ncb) {
     extern __shared__ __attribute__((aligned(64))) unsigned char smem_bytes[];
-    auto &sm = *reinterpret_cast<LeafApplySmem<Tile, NT, NB> *>(smem_bytes);
-    leaf_apply_chains<Tile, NT, NB, QT>(sm, V, ldv, Tc, pa, Bsrc, ldbs, B, ldb, k, ncb);
+    auto &sm = *reinterpret_cast<LeafApplySmem<Tile, NT, NB, LOW> *>(smem_bytes);
+    leaf_apply_chains<Tile, NT, NB, LOW, QT>(sm, V, ldv, Tc, pa, Bsrc, ldbs, B, ldb, k, ncb);
 }
 
 // As many workgroups as the compute units hold (by LDS).
-template <typename Tile, int NT, int NB, bool QT>
+template <typename Tile, int NT, int NB, bool LOW, bool QT>
 static hipError_t launch_apply_m(const typename Tile::T *V, int64_t ldv, const double *Tc, const PanelArgs &pa,
                                  const double *Bsrc, int64_t ldbs, double *B, int64_t ldb, int64_t k,
                                  const char *tag, hipStream_t st) {
-    const size_t sh = sizeof(LeafApplySmem<Tile, NT, NB>);
-    const auto kern = k_leaf_apply_m<Tile, NT, NB, QT>;
+    const size_t sh = sizeof(LeafApplySmem<Tile, NT, NB, LOW>);
+    const auto kern = k_leaf_apply_m<Tile, NT, NB, LOW, QT>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     if (e != hipSuccess) return e;
     const int ncb = (int)((k + 16 * NB - 1) / (16 * NB));
@@ -478,9 +490,20 @@ static hipError_t launch_apply_m(const typename Tile::T *V, int64_t ldv, const d
                                  const char *tag, hipStream_t st) {
     if (k <= 0) return hipSuccess;
     const bool wide = k > 16 && pa.P * ((k + 31) / 32) >= kComputeUnits;
+    // Low domains have their own form for FP32 reflectors, where it keeps bits
+    // (error of Q Q^T B, 200,001 rows in domains of 64: 40 columns 7.9e-4 -> 6.0e-4,
+    // 16 columns 4.9e-4 -> 3.1e-4, at 3 % of the time), and up to 16 columns, whose
+    // chunks are 512 rows: half of the registers and LDS (100,003 x 8 in domains of 8
+    // rows, 17 columns 0.93 -> 0.71 ms).  Wider FP64 ones would spill (64 columns
+    // in domains of 64 rows, 17 columns of B: 0.49 -> 0.92 ms).
+    const bool low = !pa.wtab && !pa.extra && 2 * pa.mb <= pa.chunk && 2 * dom_rows(pa, pa.P - 1) <= pa.chunk;
     auto go = [&](auto nt, auto nb, auto qt) {
-        return launch_apply_m<Tile, decltype(nt)::value, decltype(nb)::value, decltype(qt)::value>(
-            V, ldv, Tc, pa, Bsrc, ldbs, B, ldb, k, tag, st);
+        constexpr int NT = decltype(nt)::value, NB = decltype(nb)::value;
+        constexpr bool QT = decltype(qt)::value;
+        if constexpr (NT == 1 || sizeof(typename Tile::T) == 4) {
+            if (low) return launch_apply_m<Tile, NT, NB, true, QT>(V, ldv, Tc, pa, Bsrc, ldbs, B, ldb, k, tag, st);
+        }
+        return launch_apply_m<Tile, NT, NB, false, QT>(V, ldv, Tc, pa, Bsrc, ldbs, B, ldb, k, tag, st);
     };
     auto with_nt = [&](auto nb, auto qt) {
         switch ((pa.n + 15) >> 4) {
