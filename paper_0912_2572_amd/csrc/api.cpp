@@ -68,17 +68,9 @@ hipError_t leaf_apply(const tsqr_factors_s *f, const Panel &p, const double *Bsr
     const PanelArgs pa = panel_args(p, f->ws);
     const int64_t off = p.row_off + (int64_t)p.col_off * P.m;
     const double *Tc = at<double>(f, p.off_tc);
-    // few columns: the chunk-parallel three-pass form.  Where every compute unit
-    // has a domain the chained form reads V once and is faster (256 domains of
-    // two 64-column chunks 58 -> 36 us, of sixteen 340 -> 236), but a single
-    // panel's solve runs beside its tree, whose combines the chain's large
-    // workgroups hold up (1,048,576 x 64 in all: 1.72 against 1.60 ms).  FP32
-    // reflectors stay with the three-pass form, whose chain over T is FP64: the
-    // chained form's is FP32 (||B - Q Q^T B|| 1.8 to 2.5 times as large, one
-    // column of 262,144 x 128 in 256 to 2,048 domains), and a correction's
-    // accuracy is not to depend on the number of domains.
-    const bool chained = p.P >= tsqr::kComputeUnits && f->plan.panels.size() > 1 && !is_mixed(f);
-    if (k <= tsqr::kApply3MaxCols && Bsrc == B && p.off_pz && !chained) {
+    // few columns: the three-pass form where the plan has room for it (it has
+    // none where the chained form is the better one)
+    if (k <= tsqr::kApply3MaxCols && Bsrc == B && p.off_pz) {
         double *Pc = at<double>(f, p.off_pz);
         double *Zc = Pc + (size_t)p.n * 16 * (size_t)p.total_chunks;
         if (is_mixed(f))

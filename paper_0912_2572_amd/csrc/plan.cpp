@@ -218,7 +218,19 @@ int make_plan(int64_t m, int64_t n, const tsqr_opts *o, Plan *p) {
         pa.off_rdom = take(nn * (size_t)pa.P);
         pa.off_tnode = take(nn * (size_t)pa.P);
         pa.off_s = take(nn * (size_t)pa.P);
-        if (o->keep_q) pa.off_pz = take(2 * sizeof(double) * (size_t)pa.n * 16 * (size_t)pa.total_chunks);
+        // Few columns: the chunk-parallel three-pass form, which needs P_c and Z_c.
+        // Where every compute unit has a domain the chained form reads V once
+        // and is faster (256 domains of two 64-column chunks 58 -> 36 us, of
+        // sixteen 340 -> 236), but a single panel's solve runs beside its tree,
+        // whose combines the chain's large workgroups hold up (1,048,576 x 64 in
+        // all: 1.72 against 1.60 ms).  FP32 reflectors stay with the three-pass
+        // form, whose chain over T is FP64: the chained form's is FP32 (||B - Q
+        // Q^T B|| 1.8 to 2.5 times as large, one column of 262,144 x 128 in 256
+        // to 2,048 domains), and a correction's accuracy is not to depend on the
+        // number of domains.
+        const bool chained = pa.P >= kComputeUnits && np > 1 && o->prec != TSQR_MIXED;
+        if (o->keep_q && !chained)
+            pa.off_pz = take(2 * sizeof(double) * (size_t)pa.n * 16 * (size_t)pa.total_chunks);
         if (!pa.wchunk0.empty()) pa.off_wtab = take(sizeof(int64_t) * pa.wchunk0.size());
         P.panels.push_back(pa);
     }

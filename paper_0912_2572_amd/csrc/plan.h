@@ -16,14 +16,13 @@ namespace tsqr {
 constexpr int kMaxPanel = 64;     // columns handled by one leaf/tree kernel
 constexpr int kMaxN = 1024;       // documented scope (FP64)
 constexpr int kMaxMixedN = 256;   // mixed precision (the refinement's one-wave solves)
-constexpr int kThreads = 256;     // threads per workgroup of the leaf kernel
 constexpr size_t kAlign = 256;
 constexpr int kRefineBlocks = 1024;   // workgroups of the refinement's residual pass
 constexpr int64_t kMaxWeight = (int64_t)1 << 31;  // largest domain weight, and weight count
 
 // Column slots per thread of the leaf kernel for a panel of width w: 16
 // column groups x ns slots must cover w (ns = 1, 2 or 4).  Rows per chunk
-// are the device tile's (common.h: 512 for ns = 1 and 4, 256 for ns = 2).
+// are the device tile's (common.h: 512 for ns = 1, 256 for 2 and 4).
 inline int slots_for(int w) {
     int need = (w + 15) / 16;
     int ns = 1;
@@ -40,7 +39,7 @@ struct Panel {
     int64_t mb = 0, P = 0;          // domains of mb rows (the last one ragged)
     int64_t extra = 0;              // load-balanced partition: domains 0 .. extra-1
                                     // hold one chunk more than mb (mb whole chunks)
-    int ns = 0;                     // slots per thread (1, 2, 4, 8)
+    int ns = 0;                     // slots per thread (1, 2, 4)
     int64_t chunk = 0;              // rows per chunk of the leaf kernel
     int64_t cpd = 0;                // chunks in a full domain
     int64_t total_chunks = 0;
@@ -51,7 +50,7 @@ struct Panel {
     size_t off_rdom = 0;            // P x n x n              (domain R / node U)
     size_t off_tnode = 0;           // P x n x n              (node T, by right child)
     size_t off_s = 0;               // P x n x n              (top-down blocks)
-    size_t off_pz = 0;              // 2 x total_chunks x n x 16 (few-column apply: P_c, Z_c)
+    size_t off_pz = 0;              // 2 x total_chunks x n x 16 (few-column apply: P_c, Z_c), or 0: chained form
     // weighted partition (opts.domain_weights): first chunk of every domain,
     // P + 1 entries (the last = the panel's chunk count), on the host and,
     // copied there by the factorization, in the workspace

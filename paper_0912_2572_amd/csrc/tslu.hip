@@ -134,18 +134,6 @@ struct SelStep {
     }
 };
 
-// The unit-lower solve u <- L11^{-1} u, row j of -L11 in lane j of every
-// 16-lane row (column K: nl[K]).
-template <int K>
-struct UnitLowerSolve {
-    __device__ __forceinline__ static void run(double (&u)[16], const double (&nl)[16]) {
-        if constexpr (K < 15) {
-            row_terms<K + 1>(u, nl[K], u[K]);
-            UnitLowerSolve<K + 1>::run(u, nl);
-        }
-    }
-};
-
 // U rows of a panel for column slot s: u = L11^{-1} S[row(k)][slot s], rows
 // row(k), k = 0..15, of the stack S in pivot order (row_at: lane k's row).
 __device__ __forceinline__ void panel_u(const double *S, int row_at, int p, int s, double (&u)[16]) {
@@ -162,13 +150,13 @@ __device__ __forceinline__ void panel_u(const double *S, int row_at, int p, int 
         const int row = __builtin_amdgcn_readlane(row_at, k);
         u[k] = S[row * kSelLd + 16 * s + cg];
     }
-    UnitLowerSolve<0>::run(u, nl);
+    lower_solve<0>(u, nl, [](double v, int) { return v; });
 }
 
-// C -= L U for the 16-row tiles a0 .. NT - 1 of a stack (S: their first row),
-// panel p, slots s0 .. s1 - 1; U: 16 rows of stride kSelLd.
+// C -= L U for NT 16-row tiles of a stack (S: their first row), panel p, slots
+// s0 .. s1 - 1; U: 16 rows of stride kSelLd.
 template <int NT>
-__device__ __forceinline__ void rank16_update(double *S, const double *U, int p, int a0, int s0, int s1) {
+__device__ __forceinline__ void rank16_update(double *S, const double *U, int p, int s0, int s1) {
     const int lane = threadIdx.x & 63, cg = lane & 15, rg = lane >> 4;
     double av[NT][4];
 #pragma unroll
@@ -190,10 +178,8 @@ __device__ __forceinline__ void rank16_update(double *S, const double *U, int p,
             for (int a = 0; a < NT; ++a) c[a] = mfma_f64(av[a][kb], bv[kb], c[a]);
 #pragma unroll
         for (int a = 0; a < NT; ++a)
-            if (a >= a0) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) S[(16 * a + 4 * r + rg) * kSelLd + 16 * s + cg] = c[a][r];
-            }
+            for (int r = 0; r < 4; ++r) S[(16 * a + 4 * r + rg) * kSelLd + 16 * s + cg] = c[a][r];
     }
 }
 
@@ -251,7 +237,7 @@ __device__ __forceinline__ int select_stack(SelSmem<R> &sm, int rows, int b) {
             }
         }
         __syncthreads();
-        rank16_update<R>(sm.S + 16 * R * w * kSelLd, sm.U, p, 0, p + 1, np);
+        rank16_update<R>(sm.S + 16 * R * w * kSelLd, sm.U, p, p + 1, np);
         __syncthreads();
     }
     const int32_t g = (t < kb) ? sm.gidx[sm.sel[t]] : 0;
@@ -411,7 +397,7 @@ void k_tslu_u(const double *__restrict__ A, int64_t lda, int b, const int32_t *_
         }
         __syncthreads();
         // the rows below the panel take its update, a tile per wave
-        if (w > p) rank16_update<1>(S + 16 * w * kSelLd, Up, p, 0, p + 1, np);
+        if (w > p) rank16_update<1>(S + 16 * w * kSelLd, Up, p, p + 1, np);
         __syncthreads();
     }
     if (i < b) {
