@@ -502,11 +502,12 @@ TSQR_API size_t tsqr_batch_workspace_bytes(int count, const tsqr_batch_item *ite
    aligned, >= tsqr_batch_workspace_bytes) on `stream`, and returns a host
    handle.  refine_sweeps: refinement sweeps after the first solve for the
    mixed matrices (each stops early on its own once its estimated remaining
-   error (||dx|| times the observed contraction) is <= refine_tol ||x||
-   (tsqr_opts.refine_tol) or it stalls; the sweeps are part of the captured graph, so no host
-   synchronisation happens inside a run).  Errors: -1 count, -2 items (an
-   item out of scope: its index is reported by tsqr_batch_bad_item), -3 tune,
-   -5 refine arguments, TSQR_ERR_WORKSPACE, -1000-e. */
+   error (||dx|| times the observed contraction) is <= refine_tol ||x||, as
+   tsqr_opts.refine_tol says, or it stalls; the sweeps are part of the
+   captured graph, so no host synchronisation happens inside a run).
+   Errors: -1 count, -2 items (an item out of scope: its index is reported by
+   tsqr_batch_bad_item), -3 tune, -5 refine arguments, TSQR_ERR_WORKSPACE,
+   -1000-e. */
 TSQR_API int tsqr_batch_create(int count, const tsqr_batch_item *items, const tsqr_tune_entry *tune,
                                int ntune, int refine_sweeps, double refine_tol, void *dwork,
                                size_t work_bytes, void *stream, tsqr_batch *out);

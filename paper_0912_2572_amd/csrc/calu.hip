@@ -15,7 +15,8 @@
 //                  takes the L row of the original row that the interchanges
 //                  brought there);
 //   k_calu_trsm    U12 = L11^{-1} A12 by forward substitution (unit
-//                  diagonal), one thread per column, L11 in LDS;
+//                  diagonal), 16 columns a wave in four 16-row tiles, each
+//                  applied to the later ones on the matrix cores;
 //   k_lu_update    A22 -= L21 U12 on the FP64 matrix cores, 64 x 64 tiles,
 //                  operands staged through LDS in 16-deep chunks.
 #include "common.h"

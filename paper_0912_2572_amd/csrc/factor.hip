@@ -15,7 +15,7 @@
 // What bounds the kernel: the column steps' latency (64 of ~900 cycles per
 // 256-row chunk, one workgroup per CU when there are as many domains as CUs)
 // and then the matrix cores' 312 FP64 products per wave and chunk (20,000
-// cycles of ~115,000).  Leaf of 1,048,576 x 64 in 256 domains: 0.79 ms, 1.37
+// cycles of ~115,000).  Leaf of 1,048,576 x 64 in 256 domains: 0.79 ms, 1.53
 // TB/s of A, V and T (1.49 ms with column steps over all 64 columns); x 32:
 // 0.30 (0.69); x 16: 0.09 (0.26).
 #include <type_traits>
@@ -213,8 +213,9 @@ __device__ __forceinline__ void store_upper(const double *lds, int ld, double *_
 // bursts: the steps of panel 0 load the chunk's slots 1 .. NS - 1 (which they
 // do not touch) and slot 0 of the next chunk (into registers of its own),
 // and the steps of a later panel store the reflectors of the panel before.
-// Only the last domain can end in a partial chunk, which is loaded with
-// masking, all of it before its steps.
+// A domain's last chunk may be a partial one (the last domain's, or every
+// domain's if the row block is not a whole number of chunks): it is loaded
+// with masking, all of it before its steps.
 template <int NS, typename VT, bool VEC>
 __device__ __forceinline__ void leaf_domain(LeafSmem<NS> &sm, const double *__restrict__ A, int64_t lda,
                                             VT *__restrict__ V, int64_t ldv, double *__restrict__ Tc,

@@ -322,8 +322,9 @@ int proj_blocks(int64_t m) {
 }
 
 // The streaming form's workgroups: 8 waves where two a SIMD fit its registers
-// (NT NJ <= 8), else 4; as many as the compute units hold, fewer where a wave
-// would have no tile; where partials are kept, no more than `slots` of them.
+// (NT NJ <= 8), else 4; one per compute unit, fewer where a wave would have no
+// tile; where partials are kept, no more than `slots` of them (one for about
+// 4,096 rows).
 template <int NT, int NJ, bool UPD, bool PART>
 static hipError_t proj_stream(const double *V, int64_t ldv, int nv, const double *H, int64_t ldh, double *W,
                               int64_t ldw, int b, int64_t m, double *Hpart, int64_t slots, int *nblk,

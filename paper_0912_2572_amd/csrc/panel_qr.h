@@ -13,8 +13,9 @@
 // The columns go in panels of 16 (one slot):
 //   * 16 column steps touch only the panel's slot.  The step's column is
 //     broadcast inside every 16-lane row by one DPP move per row of the tile
-//     (no LDS, no shuffle), the dots are summed over the four lane rows by
-//     permlane swaps and over the waves through LDS behind one barrier;
+//     (no LDS, no shuffle), the dots are summed over the four lane rows by one
+//     4x4x4 matrix product with ones and over the waves through LDS behind one
+//     barrier;
 //   * the panel's 16 x 16 T grows by a column per step (rows on lanes) while
 //     the step waits for its barrier;
 //   * the other slots get the panel as one compact-WY update (Sec. 2.2,

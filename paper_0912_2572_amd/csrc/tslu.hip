@@ -14,7 +14,8 @@
 //                 shapes): the left's candidates stacked on each right's,
 //                 as the leaf's stacks;
 //   k_tslu_u      U and the unit lower L11 of A[ipiv, :] without pivoting;
-//   k_tslu_l      l_i = a_i U^{-1} for every row (one row per thread);
+//   k_tslu_l      l_i = a_i U^{-1} for every row: one row per thread, or, for
+//                 up to 16,384 rows, 16 rows a wave (k_tslu_l16);
 //   k_tslu_scatter  rows ipiv[k] of L <- row k of L11.
 //
 // Selection on a stack (select_stack): the stack's rows sit in LDS.  The
