@@ -22,7 +22,7 @@ from test_gpu_parity import colwise, dev, host, rel, tl  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# 263 domains of 64 rows and a last one of 81; of 520 rows and a last one of 9 more
+# 263 domains of 64 (520) rows, the last with the rest or, where the rest has n rows, a 264th
 @pytest.mark.parametrize("mb,extra,n,k", [(64, 17, n, k) for n in (8, 24, 40, 64) for k in (17, 31, 33, 50)] +
                          [(520, 9, n, k) for n in (8, 16, 40, 64) for k in (17, 50)] +
                          [(256, 5, 8, 33), (250, 7, 16, 33)])
